@@ -45,7 +45,8 @@ typedef int32_t ek_status;
 #define EK_ENONFINITE (-5) /* a NaN or Inf was found by ek_observables */
 #define EK_ESTATE (-6)     /* call not valid in the context's current state */
 
-#define EK_POISSON_AUTO 0 /* multigrid when every axis divides by 4, else SOR */
+#define EK_POISSON_AUTO 0 /* multigrid when every axis divides by 4 and on lattices small enough to be solved in
+                             one workgroup (at most 4096 sites, any axes), else SOR */
 #define EK_POISSON_SOR 1  /* red-black successive over-relaxation */
 #define EK_POISSON_MG 2   /* geometric multigrid V-cycles (EINVAL if the lattice cannot be coarsened) */
 #define EK_POISSON_FFT 3  /* the lagged Fourier scheme of Sec. II D, periodic lattices only: each step solves
@@ -166,7 +167,7 @@ typedef struct ek_obs {
                               not measured) */
     int64_t poisson_iters; /* iterations (SOR sweeps or V-cycles) of the last solve */
     int64_t poisson_total; /* iterations summed over all solves since ek_init */
-    int32_t poisson_mg_levels; /* multigrid levels in use (0: SOR) */
+    int32_t poisson_mg_levels; /* multigrid levels in use, the lattice included (0: SOR) */
     int64_t steps;         /* steps taken since ek_init */
     double drift[3];       /* mean particle displacement since ek_init */
     double pmomentum[3];   /* total particle momentum */
@@ -296,7 +297,8 @@ ek_status ek_init_ws(const ek_params* p, const double* rho_a, const double* rho_
    exchange, and the particle update (Sec. II E).  Each solve starts from the potential
    extrapolated in time as ek_params.phi_history says (default: adaptive, the order 2 or 3
    whose last start residual was smaller).  Work is enqueued on the context's stream.  With
-   poisson_cycles = 0 the Poisson convergence test reads residuals back to the host; with
+   poisson_cycles = 0 the Poisson convergence test reads residuals back to the host (a lattice
+   solved in one workgroup tests on the device, and the host waits once per call); with
    poisson_cycles > 0 nothing is read back and the call returns without waiting.  Returns
    EK_ENOCONV if a solve stopped at maxit (the step is still taken with the last iterate). */
 ek_status ek_step(struct ek_ctx* ctx, int32_t nsteps);
@@ -309,7 +311,7 @@ ek_status ek_step(struct ek_ctx* ctx, int32_t nsteps);
    red-black colouring, and its SOR sweeps take three colours).  iters, rel_res may be
    NULL.  Returns EK_ENOCONV if the tolerance was not met (phi keeps the last iterate).
    Multigrid solves of a context's own potential work on colour-split copies of the
-   potential and charge; with EK_POISSON_SITE_ORDER=1 in the environment at ek_init the
+   potential and charge (lattices of more than 4096 sites); with EK_POISSON_SITE_ORDER=1 in the environment at ek_init the
    context keeps them in site order instead (a diagnostic: the results are bit-identical). */
 ek_status ek_poisson(struct ek_ctx* ctx, double tol, int32_t maxit, int32_t* iters, double* rel_res);
 
@@ -328,7 +330,9 @@ ek_status ek_set_field(struct ek_ctx* ctx, const double* E_ext);
    (fine_pre, fine_post), on the coarse grids smoothed by separate launches (coarse_pre,
    coarse_post) and on the upper grid of the last two, which one workgroup handles in LDS
    (tail_pre, tail_post); red-black SOR sweeps on the coarsest grid; omega relaxes the
-   smoothing sweeps (1 is Gauss-Seidel).  Defaults 1, 2, 1, 2, 3, 3, 10, 1.2.  Counts in
+   smoothing sweeps (1 is Gauss-Seidel).  A lattice solved in one workgroup takes the counts of
+   the lattice and of the coarse grids (one more before the correction) and omega, and solves
+   its coarsest grid directly.  Defaults 1, 2, 1, 2, 3, 3, 10, 1.2.  Counts in
    0..64, omega in (0, 2); the lattice needs at least one sweep per cycle.  The solve still
    runs to the Poisson tolerance; the shape only trades work per cycle against cycles.
    Errors: EK_EINVAL, EK_ESTATE. */

@@ -15,7 +15,7 @@
 
 #include "ek.h"
 #include "ek_device.h"
-#include "ek_internal.h"
+#include "ek_gmg.h"
 #include "ek_lattice.h"
 
 using namespace ek;
@@ -30,6 +30,10 @@ struct TimeRec {
     int cls;
     int count;
 };
+
+// Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
+// from kCtl on the state of the single-workgroup solve.
+constexpr int kCtl = 32, kScal = kCtl + kCtlCount;
 
 struct ek_ctx {
     ek_params p{};
@@ -117,6 +121,15 @@ struct ek_ctx {
     double rate = -1.0;
     // multigrid (levels[0] is the lattice itself and holds no arrays)
     std::vector<MGLevel> mg;
+    // hierarchy with per-axis coarsening (ek_gmg.h) and its axis tables on the device;
+    // small: the whole solve runs in one workgroup (k_small_solve)
+    GHier gh;
+    GSub gsub{};
+    uint32_t* gt_pn = nullptr;
+    float* gt_w = nullptr;
+    int* gt_first = nullptr;
+    float* gt_ratio = nullptr;
+    bool small = false;
     double mg_coarse_omega = 1.0;
     // V-cycle shape: red-black sweeps before and after the coarse correction on the
     // lattice and on the coarse grids, and sweeps on the coarsest grid
@@ -711,9 +724,66 @@ static void mg_build(ek_ctx* c, const Fields<T>& F) {
     }
 }
 
+// The shape of a hierarchy with per-axis coarsening: one more sweep before the correction on
+// its coarse grids than on launched ones (they cost little in LDS, and an 8x8x48 column
+// takes 7.8 instead of 9.9 cycles).
+static GShape gmg_shape(const ek_ctx* c) {
+    return GShape{c->mg_fine_pre, c->mg_fine_post, c->mg_pre + 1, c->mg_post, c->mg_omega};
+}
+
+// One solve in a single workgroup; step: from the extrapolated start, as part of ek_step.
+template <typename T>
+static void small_solve(ek_ctx* c, double tol, int maxit, bool step) {
+    Timer tm(c, EK_T_POISSON);
+    EK_KT(EK_K_TAIL);
+    const GTab tab{c->gt_pn, c->gt_w, c->gt_first, c->gt_ratio};
+    const SmallArgs a{gmg_shape(c), tol, maxit, step ? c->fixed_cycles : 0, step ? 1 : 0, c->phi_history,
+                      c->phi_prev, c->phi_prev2, c->scal + kCtl};
+    launch_small_solve<T>(c->S, fields<T>(c), c->gsub, tab, a, c->st);
+}
+
+// The device's solver state from the host's record, and back (the latter waits).
+static ek_status small_state_up(ek_ctx* c) {
+    double* h = c->hscal + kCtl;
+    for (int k = 0; k < kCtlCount; ++k) h[k] = 0.0;
+    h[kCtlRel0] = c->rel0_of[2];
+    h[kCtlRel0 + 1] = c->rel0_of[3];
+    h[kCtlOrder] = c->ws_order;
+    h[kCtlSince] = c->ws_since;
+    h[kCtlSteps] = (double)c->steps;
+    EK_HIP(hipMemcpyAsync(c->scal + kCtl, h, kCtlCount * sizeof(double), hipMemcpyHostToDevice, c->st));
+    return EK_OK;
+}
+static ek_status small_state_down(ek_ctx* c) {
+    EK_HIP(hipGetLastError());
+    EK_HIP(hipMemcpyAsync(c->hscal, c->scal, kScal * sizeof(double), hipMemcpyDeviceToHost, c->st));
+    EK_HIP(hipStreamSynchronize(c->st));
+    const double* h = c->hscal + kCtl;
+    c->rel0_of[2] = h[kCtlRel0];
+    c->rel0_of[3] = h[kCtlRel0 + 1];
+    c->ws_order = (int)h[kCtlOrder];
+    c->ws_since = (int)h[kCtlSince];
+    c->last_mean = c->hscal[0];
+    c->last_iters = (int)h[kCtlIters];
+    c->last_rel = h[kCtlRel];
+    c->last_rel0 = h[kCtlRelStart];
+    c->rel_max = std::max(c->rel_max, h[kCtlRelMax]);
+    c->ptotal += (long long)h[kCtlTotal];
+    if (h[kCtlNoConv] != 0.0) return fail(c, EK_ENOCONV, "Poisson solve stopped at maxit above the tolerance");
+    return EK_OK;
+}
+
 // Requires q, eps and the source mean of the current state on the device.
 template <typename T>
 static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out, double* rel_out, bool fixed = false) {
+    if (c->small) {
+        EK_TRY(small_state_up(c));
+        small_solve<T>(c, tol, maxit, false);
+        const ek_status st = small_state_down(c);
+        if (iters_out) *iters_out = c->last_iters;
+        if (rel_out) *rel_out = c->last_rel;
+        return st;
+    }
     Timer tm(c, EK_T_POISSON);
     Fields<T> F = fields<T>(c);
     const bool use_mg = !c->mg.empty();
@@ -911,6 +981,7 @@ static void moments_pass(ek_ctx* c) {
         EK_KT(EK_K_VIRTUAL);
         launch_virtual<T>(c->S, F, c->st);
     }
+    if (c->small) return;  // summed by the solve itself
     EK_KT(EK_K_SOURCE_MEAN);
     launch_source_mean(c->S, c->red, c->nblk, c->scal, c->st);
 }
@@ -981,6 +1052,21 @@ static ek_status lagged_fourier(ek_ctx* c) {
 template <typename T>
 static ek_status step_impl(ek_ctx* c, int nsteps) {
     ek_status worst = EK_OK;
+    if (c->small && nsteps > 0) {
+        // The solve keeps its convergence test and its warm-start choice on the device, so the
+        // steps of a call are enqueued one after another and the host reads back once.
+        const bool fixed = c->fixed_cycles > 0;
+        if (!fixed) EK_TRY(small_state_up(c));
+        for (int s = 0; s < nsteps; ++s) {
+            moments_pass<T>(c);
+            small_solve<T>(c, c->p.poisson_tol, c->p.poisson_maxit, true);
+            EK_TRY(step_rest<T>(c));
+        }
+        if (!fixed) return small_state_down(c);
+        c->last_iters = c->fixed_cycles;
+        c->ptotal += (long long)c->fixed_cycles * nsteps;
+        return EK_OK;
+    }
     for (int s = 0; s < nsteps; ++s) {
         moments_pass<T>(c);
         if (c->fft) {
@@ -1102,7 +1188,7 @@ static ek_status allocate_all(ek_ctx* c, const HostGeom& g, int np) {
         EK_TRY(dalloc(c, (void**)&c->blk, (size_t)(N / 2) * 8));
     }
     EK_TRY(dalloc(c, (void**)&c->red, (size_t)c->nblk * kRedSlots * 8));
-    EK_TRY(dalloc(c, (void**)&c->scal, 32 * 8));
+    EK_TRY(dalloc(c, (void**)&c->scal, kScal * 8));
     EK_TRY(dalloc(c, (void**)&c->obs_max, 16 * sizeof(int)));
     EK_TRY(dalloc(c, (void**)&c->stage, (size_t)N * 8));
     EK_TRY(dalloc(c, (void**)&c->stage2, (size_t)N * 8));
@@ -1112,6 +1198,12 @@ static ek_status allocate_all(ek_ctx* c, const HostGeom& g, int np) {
         EK_TRY(dalloc(c, (void**)&L.ax, (size_t)L.n * 8));
         EK_TRY(dalloc(c, (void**)&L.ay, (size_t)L.n * 8));
         EK_TRY(dalloc(c, (void**)&L.az, (size_t)L.n * 8));
+    }
+    if (c->small) {
+        EK_TRY(dalloc(c, (void**)&c->gt_pn, c->gh.pn.size() * 4));
+        EK_TRY(dalloc(c, (void**)&c->gt_w, c->gh.w.size() * 4));
+        EK_TRY(dalloc(c, (void**)&c->gt_first, c->gh.first.size() * 4));
+        EK_TRY(dalloc(c, (void**)&c->gt_ratio, c->gh.ratio.size() * 4));
     }
     if (!g.vlist.empty()) EK_TRY(dalloc(c, (void**)&c->vlist, g.vlist.size() * 4));
     if (c->S.reproject) {  // room for every box site (the particle-path sites all lie in the boxes)
@@ -1210,7 +1302,7 @@ static ek_status init_impl(ek_ctx* c, const double* rho_a, const double* rho_b, 
         for (int b = 0; b < 2; ++b) EK_HIP(hipMemsetAsync(c->ms[b], 0, 8 * (size_t)N * es, c->st));
     c->phi_own = c->phi;
     c->q_own = c->q;
-    EK_HIP(hipHostMalloc((void**)&c->hscal, 32 * sizeof(double), hipHostMallocDefault));
+    EK_HIP(hipHostMalloc((void**)&c->hscal, kScal * sizeof(double), hipHostMallocDefault));
     for (auto& L : c->mg) EK_HIP(hipMemsetAsync(L.phi, 0, (size_t)L.n * 8, c->st));
     for (int b = 0; b < 2; ++b)
         for (int k = 0; k < 2; ++k) {
@@ -1222,11 +1314,18 @@ static ek_status init_impl(ek_ctx* c, const double* rho_a, const double* rho_b, 
     if (c->mlo) EK_HIP(hipMemsetAsync(c->mlo, 0, 2 * (size_t)N * es, c->st));
     EK_HIP(hipMemsetAsync(c->uph, 0, 3 * (size_t)N * es, c->st));
     EK_HIP(hipMemsetAsync(c->phi, 0, (size_t)N * 8, c->st));
-    EK_HIP(hipMemsetAsync(c->scal, 0, 32 * 8, c->st));
+    EK_HIP(hipMemsetAsync(c->scal, 0, kScal * 8, c->st));
     int hmax[16] = {0};
     hmax[8] = 1;
     EK_HIP(hipMemcpyAsync(c->obs_max, hmax, sizeof(hmax), hipMemcpyHostToDevice, c->st));
     EK_HIP(hipStreamSynchronize(c->st));  // hmax is a stack array
+
+    if (c->small && !c->gh.levels.empty()) {
+        EK_HIP(hipMemcpyAsync(c->gt_pn, c->gh.pn.data(), c->gh.pn.size() * 4, hipMemcpyHostToDevice, c->st));
+        EK_HIP(hipMemcpyAsync(c->gt_w, c->gh.w.data(), c->gh.w.size() * 4, hipMemcpyHostToDevice, c->st));
+        EK_HIP(hipMemcpyAsync(c->gt_first, c->gh.first.data(), c->gh.first.size() * 4, hipMemcpyHostToDevice, c->st));
+        EK_HIP(hipMemcpyAsync(c->gt_ratio, c->gh.ratio.data(), c->gh.ratio.size() * 4, hipMemcpyHostToDevice, c->st));
+    }
 
     // geometry upload
     c->hflags = g.flags;
@@ -1480,17 +1579,28 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
     if (p->poisson_cycles > 0 && (c->mg.empty() || c->fft))
         return fail(c, EK_EINVAL, "a fixed V-cycle count needs the multigrid solver");
     c->fixed_cycles = p->poisson_cycles;
+    c->esz = p->precision == EK_FP32 ? 4 : 8;
+    // A lattice of at most 4096 sites that fits one workgroup's LDS with its coarse grids is
+    // solved there by one launch: below that size every launch of a cycle is latency.  At the
+    // upper end 16^3 takes 152 us per step there against 268 with launches; a 4x4x128 column,
+    // whose coarsest launched grid (2x2x64) ten sweeps do not solve, 106 against 2840.
+    if (p->poisson_solver != EK_POISSON_SOR && !c->fft) {
+        const int dims[3] = {S.nx, S.ny, S.z1 - S.z0 + 1};
+        const bool per[3] = {true, true, !S.walls};
+        gmg_hierarchy(dims, per, c->gh);
+        c->gsub = gmg_sub(c->gh, 0);
+        c->small = gmg_small_fits(c->gsub, S.ndomain);
+    }
     // EK_POISSON_SITE_ORDER=1 keeps the multigrid solves in site order (a diagnostic switch:
     // the results are the same, bit for bit)
     const char* site_order = std::getenv("EK_POISSON_SITE_ORDER");
-    c->split_layout = !c->mg.empty() && !(site_order && std::atoi(site_order) != 0);
+    c->split_layout = !c->mg.empty() && !c->small && !(site_order && std::atoi(site_order) != 0);
     // EK_POISSON_ONE_PASS=1 runs the lattice sweeps of colour-split solves in one pass
     // (k_sor_rb) where it fits.  The results are the same, bit for bit; on gfx950 the two
     // colour passes are faster (the one-pass kernel is bound by its FP64 rows, recomputed on
     // the ring), so they are the default.
     const char* one_pass = std::getenv("EK_POISSON_ONE_PASS");
     c->one_pass = one_pass && std::atoi(one_pass) != 0;
-    c->esz = p->precision == EK_FP32 ? 4 : 8;
     return EK_OK;
 }
 
@@ -1602,7 +1712,7 @@ static ek_status observe_impl(ek_ctx* c, ek_obs* o) {
     }
     o->poisson_iters = c->last_iters;
     o->poisson_total = c->ptotal;
-    o->poisson_mg_levels = c->mg.empty() ? 0 : (int32_t)c->mg.size() + 1;
+    o->poisson_mg_levels = c->small ? (int32_t)c->gh.levels.size() + 1 : (c->mg.empty() ? 0 : (int32_t)c->mg.size() + 1);
     o->steps = c->steps;
     if (c->np > 0) {
         std::vector<double> hx(3 * c->np), hv(3 * c->np);
