@@ -45,10 +45,10 @@ typedef int32_t ek_status;
 #define EK_ENONFINITE (-5) /* a NaN or Inf was found by ek_observables */
 #define EK_ESTATE (-6)     /* call not valid in the context's current state */
 
-#define EK_POISSON_AUTO 0 /* multigrid when every axis divides by 4 and on lattices small enough to be solved in
-                             one workgroup (at most 4096 sites, any axes), else SOR */
+#define EK_POISSON_AUTO 0 /* multigrid: axes halved while all divide by 4, or each axis coarsened by itself where that
+                             stops too early (odd or short axes, lattices solved in one workgroup) */
 #define EK_POISSON_SOR 1  /* red-black successive over-relaxation */
-#define EK_POISSON_MG 2   /* geometric multigrid V-cycles (EINVAL if the lattice cannot be coarsened) */
+#define EK_POISSON_MG 2   /* the same, EINVAL unless every axis divides by 4 (and the coarsest grid is small) */
 #define EK_POISSON_FFT 3  /* the lagged Fourier scheme of Sec. II D, periodic lattices only: each step solves
                              L phi = r once by FFT, L the 7-point Laplacian and
                              r = [-s - sum_f (eps_j - eps_i)(phi_old_j - phi_old_i)/2] / eps with the
@@ -308,11 +308,12 @@ ek_status ek_step(struct ek_ctx* ctx, int32_t nsteps);
    charge), eps_face the mean of the two sites, source projected to zero mean, gauge
    mean(phi) = 0, starting from the current potential with the context's solver
    (multigrid V-cycles or red-black SOR; a lattice with an odd periodic y or z axis has no
-   red-black colouring, and its SOR sweeps take three colours).  iters, rel_res may be
+   red-black colouring, and its sweeps take three colours).  iters, rel_res may be
    NULL.  Returns EK_ENOCONV if the tolerance was not met (phi keeps the last iterate).
    Multigrid solves of a context's own potential work on colour-split copies of the
-   potential and charge (lattices of more than 4096 sites); with EK_POISSON_SITE_ORDER=1 in the environment at ek_init the
-   context keeps them in site order instead (a diagnostic: the results are bit-identical). */
+   potential and charge (where the axes halve far enough and the lattice is not solved in one
+   workgroup); with EK_POISSON_SITE_ORDER=1 in the environment at ek_init the context keeps
+   them in site order instead (a diagnostic: the results are bit-identical). */
 ek_status ek_poisson(struct ek_ctx* ctx, double tol, int32_t maxit, int32_t* iters, double* rel_res);
 
 /* Change the external field E_ext (3 doubles, lattice units) of a running context; it takes
@@ -330,9 +331,9 @@ ek_status ek_set_field(struct ek_ctx* ctx, const double* E_ext);
    (fine_pre, fine_post), on the coarse grids smoothed by separate launches (coarse_pre,
    coarse_post) and on the upper grid of the last two, which one workgroup handles in LDS
    (tail_pre, tail_post); red-black SOR sweeps on the coarsest grid; omega relaxes the
-   smoothing sweeps (1 is Gauss-Seidel).  A lattice solved in one workgroup takes the counts of
-   the lattice and of the coarse grids (one more before the correction) and omega, and solves
-   its coarsest grid directly.  Defaults 1, 2, 1, 2, 3, 3, 10, 1.2.  Counts in
+   smoothing sweeps (1 is Gauss-Seidel).  A lattice coarsened axis by axis takes the counts of the
+   lattice and of the launched coarse grids and omega; the grids held in one workgroup take
+   those too (one more before the correction), the coarsest of them is solved directly.  Defaults 1, 2, 1, 2, 3, 3, 10, 1.2.  Counts in
    0..64, omega in (0, 2); the lattice needs at least one sweep per cycle.  The solve still
    runs to the Poisson tolerance; the shape only trades work per cycle against cycles.
    Errors: EK_EINVAL, EK_ESTATE. */

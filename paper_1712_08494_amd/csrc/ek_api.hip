@@ -130,6 +130,12 @@ struct ek_ctx {
     int* gt_first = nullptr;
     float* gt_ratio = nullptr;
     bool small = false;
+    // gmg: V-cycles on this hierarchy with the lattice and its upper grids launched; gt, gm: the
+    // launched grids and the first of those of the tail kernel; g_rows: the tail's rows
+    bool gmg = false;
+    std::vector<GTrans> gt;
+    std::vector<MGLevel> gm;
+    void* g_rows = nullptr;
     double mg_coarse_omega = 1.0;
     // V-cycle shape: red-black sweeps before and after the coarse correction on the
     // lattice and on the coarse grids, and sweeps on the coarsest grid
@@ -569,12 +575,19 @@ static ek_status check_residual(ek_ctx* c, const Fields<T>& F, bool split, bool 
     return EK_OK;
 }
 
+template <typename T>
+static void gmg_vcycle(ek_ctx* c, const Fields<T>& F);
+
 // One V-cycle on the lattice (grid 0) with the coarse grids c->mg[0..nl-1] (grid g >= 1 is
 // c->mg[g - 1]).  The last one or two grids are handled by the single-workgroup tail
 // kernel (the coarsest solve, and the sweeps of the grid above it when small enough).
 // split: F holds the colour-split lattice potential and charge.
 template <typename T>
 static void vcycle(ek_ctx* c, const Fields<T>& F0, bool split) {
+    if (c->gmg) {
+        gmg_vcycle<T>(c, F0);
+        return;
+    }
     const int nl = (int)c->mg.size();
     const int tail_mid = (nl >= 2 && c->mg[nl - 2].n <= 4096 && c->mg[nl - 1].n <= 512) ? 1 : 0;
     const int last_gpu = nl - 1 - tail_mid;  // finest grid handled by the tail, minus one
@@ -666,6 +679,67 @@ static void vcycle(ek_ctx* c, const Fields<T>& F0, bool split) {
     }
 }
 
+static GTab gmg_tables(const ek_ctx* c) { return GTab{c->gt_pn, c->gt_w, c->gt_first, c->gt_ratio}; }
+
+// The shape of a hierarchy with per-axis coarsening: one more sweep before the correction on
+// the coarse grids of a workgroup than on launched ones (they cost little in LDS, and an
+// 8x8x48 column takes 7.8 instead of 9.9 cycles).
+static GShape gmg_shape(const ek_ctx* c) {
+    return GShape{c->mg_fine_pre, c->mg_fine_post, c->mg_pre + 1, c->mg_post, c->mg_omega};
+}
+
+// One V-cycle on the hierarchy with per-axis coarsening: site-order lattice, launched grids
+// c->gm[0 .. last - 1], the rest in the tail kernel.
+template <typename T>
+static void gmg_vcycle(ek_ctx* c, const Fields<T>& F) {
+    const GTab tab = gmg_tables(c);
+    const int last = (int)c->gm.size() - 1;  // the tail's first grid
+    auto lattice = [&](int sweeps) {
+        if (sweeps <= 0) return;
+        Timer tm(c, EK_T_SMOOTH, c->S.ncolor * sweeps);
+        for (int s = 0; s < sweeps; ++s)
+            for (int color = 0; color < c->S.ncolor; ++color) {
+                EK_KT(EK_K_SOR);
+                launch_sor<T>(c->S, F, color, c->mg_omega, false, c->st);
+            }
+    };
+    auto smooth = [&](int l, int sweeps, bool skip_red) {
+        for (int s = 0; s < sweeps; ++s)
+            for (int color = skip_red && s == 0 ? 1 : 0; color < 2; ++color) {
+                EK_KT(EK_K_SMOOTH);
+                launch_mg_smooth(c->gm[l], color, c->mg_omega, c->st);
+            }
+    };
+    // the restriction into a launched grid takes that grid's first red pass
+    const double red = c->mg_pre >= 1 ? c->mg_omega : 0.0;
+    lattice(c->mg_fine_pre);
+    {
+        EK_KT(EK_K_RESTRICT_FINE);
+        launch_g_restrict0<T>(c->S, F, c->gt[0], c->gm[0], tab, last > 0 ? red : 0.0, c->st);
+    }
+    for (int l = 0; l < last; ++l) {
+        smooth(l, c->mg_pre, red > 0.0);
+        EK_KT(EK_K_RESTRICT);
+        launch_g_restrict(c->gt[l], c->gm[l], c->gt[l + 1], c->gm[l + 1], tab, l + 1 < last ? red : 0.0, c->st);
+    }
+    {
+        EK_KT(EK_K_TAIL);
+        launch_g_tail(c->gsub, tab, c->gm[last], c->g_rows, gmg_shape(c), c->st);
+    }
+    for (int l = last - 1; l >= 0; --l) {
+        {
+            EK_KT(EK_K_PROLONG);
+            launch_g_prolong(c->gt[l], c->gm[l], c->gt[l + 1], c->gm[l + 1], tab, c->st);
+        }
+        smooth(l, c->mg_post, false);
+    }
+    {
+        EK_KT(EK_K_PROLONG_FINE);
+        launch_g_prolong0<T>(c->S, F, c->gt[0], c->gm[0], tab, c->st);
+    }
+    lattice(c->mg_fine_post);
+}
+
 static void vcycle_graph_drop(ek_ctx* c) {
     if (c->vc_exec) (void)hipGraphExecDestroy(c->vc_exec);
     if (c->vc_graph) (void)hipGraphDestroy(c->vc_graph);
@@ -683,7 +757,8 @@ static bool own_solve(const ek_ctx* c) {
 // (colour-split or site order) it was captured with.
 template <typename T>
 static ek_status run_cycles(ek_ctx* c, Fields<T>& F, bool split, int k) {
-    const bool own = own_solve(c);
+    // (a captured cycle in site order holds the own potential's address: not for an adjoint solve)
+    const bool own = own_solve(c) && (split || !c->adj_solve);
     if (own && c->vc_exec && c->vc_split != split) vcycle_graph_drop(c);  // other solves launch directly
     if (c->timing < 2 && own && !c->vc_off && !c->vc_exec) {
         if (!c->cap_st) EK_HIP(hipStreamCreateWithFlags(&c->cap_st, hipStreamNonBlocking));
@@ -714,6 +789,15 @@ static ek_status run_cycles(ek_ctx* c, Fields<T>& F, bool split, int k) {
 // Coarse-level face coefficients for the current permittivity.
 template <typename T>
 static void mg_build(ek_ctx* c, const Fields<T>& F) {
+    if (c->gmg) {
+        const GTab tab = gmg_tables(c);
+        EK_KT(EK_K_COARSEN);
+        launch_g_coarsen0<T>(c->S, F, c->gt[0], c->gm[0], tab, c->st);
+        for (size_t l = 1; l < c->gm.size(); ++l)
+            launch_g_coarsen(c->gt[l - 1], c->gm[l - 1], c->gt[l], c->gm[l], tab, c->st);
+        launch_g_tail_build(c->gsub, tab, c->gm.back(), c->g_rows, c->st);
+        return;
+    }
     {
         EK_KT(EK_K_COARSEN);
         launch_mg_coarsen_fine<T>(c->S, F, c->mg[0], c->st);
@@ -724,22 +808,14 @@ static void mg_build(ek_ctx* c, const Fields<T>& F) {
     }
 }
 
-// The shape of a hierarchy with per-axis coarsening: one more sweep before the correction on
-// its coarse grids than on launched ones (they cost little in LDS, and an 8x8x48 column
-// takes 7.8 instead of 9.9 cycles).
-static GShape gmg_shape(const ek_ctx* c) {
-    return GShape{c->mg_fine_pre, c->mg_fine_post, c->mg_pre + 1, c->mg_post, c->mg_omega};
-}
-
 // One solve in a single workgroup; step: from the extrapolated start, as part of ek_step.
 template <typename T>
 static void small_solve(ek_ctx* c, double tol, int maxit, bool step) {
     Timer tm(c, EK_T_POISSON);
     EK_KT(EK_K_TAIL);
-    const GTab tab{c->gt_pn, c->gt_w, c->gt_first, c->gt_ratio};
     const SmallArgs a{gmg_shape(c), tol, maxit, step ? c->fixed_cycles : 0, step ? 1 : 0, c->phi_history,
                       c->phi_prev, c->phi_prev2, c->scal + kCtl};
-    launch_small_solve<T>(c->S, fields<T>(c), c->gsub, tab, a, c->st);
+    launch_small_solve<T>(c->S, fields<T>(c), c->gsub, gmg_tables(c), a, c->st);
 }
 
 // The device's solver state from the host's record, and back (the latter waits).
@@ -786,7 +862,7 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
     }
     Timer tm(c, EK_T_POISSON);
     Fields<T> F = fields<T>(c);
-    const bool use_mg = !c->mg.empty();
+    const bool use_mg = c->gmg || !c->mg.empty();
     const bool own = own_solve(c);
     // a multigrid solve of the context's own potential runs on colour-split copies of the
     // potential and charge; the gauge kernel writes the result back in site order
@@ -1199,7 +1275,15 @@ static ek_status allocate_all(ek_ctx* c, const HostGeom& g, int np) {
         EK_TRY(dalloc(c, (void**)&L.ay, (size_t)L.n * 8));
         EK_TRY(dalloc(c, (void**)&L.az, (size_t)L.n * 8));
     }
-    if (c->small) {
+    for (auto& L : c->gm) {
+        EK_TRY(dalloc(c, (void**)&L.phi, (size_t)L.n * 8));
+        EK_TRY(dalloc(c, (void**)&L.s, (size_t)L.n * 8));
+        EK_TRY(dalloc(c, (void**)&L.ax, (size_t)L.n * 8));
+        EK_TRY(dalloc(c, (void**)&L.ay, (size_t)L.n * 8));
+        EK_TRY(dalloc(c, (void**)&L.az, (size_t)L.n * 8));
+    }
+    if (c->gmg) EK_TRY(dalloc(c, &c->g_rows, gmg_rows_bytes(c->gsub)));
+    if (c->small || c->gmg) {
         EK_TRY(dalloc(c, (void**)&c->gt_pn, c->gh.pn.size() * 4));
         EK_TRY(dalloc(c, (void**)&c->gt_w, c->gh.w.size() * 4));
         EK_TRY(dalloc(c, (void**)&c->gt_first, c->gh.first.size() * 4));
@@ -1320,7 +1404,7 @@ static ek_status init_impl(ek_ctx* c, const double* rho_a, const double* rho_b, 
     EK_HIP(hipMemcpyAsync(c->obs_max, hmax, sizeof(hmax), hipMemcpyHostToDevice, c->st));
     EK_HIP(hipStreamSynchronize(c->st));  // hmax is a stack array
 
-    if (c->small && !c->gh.levels.empty()) {
+    if ((c->small || c->gmg) && !c->gh.levels.empty()) {
         EK_HIP(hipMemcpyAsync(c->gt_pn, c->gh.pn.data(), c->gh.pn.size() * 4, hipMemcpyHostToDevice, c->st));
         EK_HIP(hipMemcpyAsync(c->gt_w, c->gh.w.data(), c->gh.w.size() * 4, hipMemcpyHostToDevice, c->st));
         EK_HIP(hipMemcpyAsync(c->gt_first, c->gh.first.data(), c->gh.first.size() * 4, hipMemcpyHostToDevice, c->st));
@@ -1588,13 +1672,41 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
         const int dims[3] = {S.nx, S.ny, S.z1 - S.z0 + 1};
         const bool per[3] = {true, true, !S.walls};
         gmg_hierarchy(dims, per, c->gh);
-        c->gsub = gmg_sub(c->gh, 0);
+        c->gsub = gmg_sub(c->gh, 0, true);
         c->small = gmg_small_fits(c->gsub, S.ndomain);
+        // Larger lattices whose axes do not halve far enough: no V-cycle above (the automatic
+        // choice took SOR: 110 sweeps a step on 50x37x29, 319 on 4x128x128), or one whose
+        // coarsest grid is longer than ten SOR sweeps reach (13 cycles a step on 8x8x48).
+        const int axis = std::max(dims[0], std::max(dims[1], dims[2]));
+        const bool long_coarsest = !c->mg.empty() && std::max(c->mg.back().nx, std::max(c->mg.back().ny, c->mg.back().nz)) > 16;
+        const int first = gmg_tail_first(c->gh);
+        if (!c->small && (c->mg.empty() || long_coarsest) && axis <= 65535 && first >= 0) {
+            c->gmg = true;
+            c->gsub = gmg_sub(c->gh, first, false);
+            for (int l = 0; l <= first; ++l) {
+                const GLevelDesc& D = c->gh.levels[l];
+                GTrans G{};
+                MGLevel M{};
+                for (int k = 0; k < 3; ++k) G.d[k] = D.d[k], G.of[k] = D.of[k], G.oc[k] = D.oc[k];
+                G.n = M.n = D.n;
+                G.lead = D.lead;
+                G.inv_nx = 1.0 / D.d[0];
+                G.inv_ny = 1.0 / D.d[1];
+                M.nx = D.d[D.lead];
+                M.ny = D.lead < 2 ? D.d[D.lead + 1] : 1;
+                M.nz = D.lead < 1 ? D.d[2] : 1;
+                M.inv_nx = 1.0 / M.nx;
+                M.inv_ny = 1.0 / M.ny;
+                M.inv_hx = M.nx >= 2 ? 1.0 / (M.nx / 2) : 0.0;
+                c->gt.push_back(G);
+                c->gm.push_back(M);
+            }
+        }
     }
     // EK_POISSON_SITE_ORDER=1 keeps the multigrid solves in site order (a diagnostic switch:
     // the results are the same, bit for bit)
     const char* site_order = std::getenv("EK_POISSON_SITE_ORDER");
-    c->split_layout = !c->mg.empty() && !c->small && !(site_order && std::atoi(site_order) != 0);
+    c->split_layout = !c->mg.empty() && !c->small && !c->gmg && !(site_order && std::atoi(site_order) != 0);
     // EK_POISSON_ONE_PASS=1 runs the lattice sweeps of colour-split solves in one pass
     // (k_sor_rb) where it fits.  The results are the same, bit for bit; on gfx950 the two
     // colour passes are faster (the one-pass kernel is bound by its FP64 rows, recomputed on
@@ -1712,7 +1824,7 @@ static ek_status observe_impl(ek_ctx* c, ek_obs* o) {
     }
     o->poisson_iters = c->last_iters;
     o->poisson_total = c->ptotal;
-    o->poisson_mg_levels = c->small ? (int32_t)c->gh.levels.size() + 1 : (c->mg.empty() ? 0 : (int32_t)c->mg.size() + 1);
+    o->poisson_mg_levels = c->small || c->gmg ? (int32_t)c->gh.levels.size() + 1 : (c->mg.empty() ? 0 : (int32_t)c->mg.size() + 1);
     o->steps = c->steps;
     if (c->np > 0) {
         std::vector<double> hx(3 * c->np), hv(3 * c->np);
@@ -2349,7 +2461,7 @@ extern "C" int32_t ek_autotune_candidates(int32_t* shapes, double* omegas) {
 extern "C" ek_status ek_autotune_multigrid(ek_ctx* c, int32_t trial_steps, int32_t* best, double* ms_per_step) {
     if (!c || !c->phi) return EK_ESTATE;
     if (c->in_batch) return fail(c, EK_ESTATE, "replica of a batch: its cycle is fixed by the batch");
-    if (c->mg.empty()) return fail(c, EK_EINVAL, "this lattice is solved by SOR: there is no V-cycle to tune");
+    if (c->mg.empty()) return fail(c, EK_EINVAL, "the axes of this lattice do not halve: there is no V-cycle to tune");
     if (c->fft) return fail(c, EK_EINVAL, "the lagged Fourier scheme runs no V-cycles in its steps");
     if (c->S.reproject) return fail(c, EK_EINVAL, "moving particles change the geometry, which the tuner does not restore");
     if (trial_steps < 1 || trial_steps > 1000) return fail(c, EK_EINVAL, "trial_steps must be in 1..1000");

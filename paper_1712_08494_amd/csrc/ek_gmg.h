@@ -49,10 +49,12 @@ struct GLds {
 };
 struct GSub {
     int nl, cells, npn, nfirst;
+    int pn0, first0;  // where its tables start in the hierarchy's
     GLds L[kGMaxLevels];
 };
-GSub gmg_sub(const GHier& H, int first);
-size_t gmg_tail_bytes(const GSub& G);
+GSub gmg_sub(const GHier& H, int first, bool from_lattice);
+int gmg_tail_first(const GHier& H);
+size_t gmg_rows_bytes(const GSub& G);  // what launch_g_tail_build leaves for launch_g_tail
 bool gmg_small_fits(const GSub& G, unsigned ndomain);
 
 // V-cycle shape: sweeps on the lattice and on the coarse grids before and after the
@@ -78,5 +80,34 @@ struct SmallArgs {
 template <typename T>
 void launch_small_solve(const Scalars& S, const Fields<T>& F, const GSub& G, const GTab& t, const SmallArgs& a,
                         hipStream_t st);
+
+// A launched coarse grid in its own axes; the MGLevel beside it has its compact ones.
+struct GTrans {
+    int d[3];
+    unsigned n;
+    int lead, of[3], oc[3];
+    double inv_nx, inv_ny;
+};
+
+// face coefficients of grid C (from the lattice, from grid Cf), residuals restricted to it with
+// the start of its correction (red_omega > 0: with the first red pass), and its correction
+// interpolated (onto the lattice, onto grid Cf)
+template <typename T>
+void launch_g_coarsen0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                       hipStream_t st);
+void launch_g_coarsen(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                      hipStream_t st);
+template <typename T>
+void launch_g_restrict0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                        double red_omega, hipStream_t st);
+void launch_g_restrict(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                       double red_omega, hipStream_t st);
+template <typename T>
+void launch_g_prolong0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                       hipStream_t st);
+void launch_g_prolong(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                      hipStream_t st);
+void launch_g_tail_build(const GSub& G, const GTab& t, const MGLevel& M, void* rows, hipStream_t st);
+void launch_g_tail(const GSub& G, const GTab& t, const MGLevel& M, const void* rows, const GShape& sh, hipStream_t st);
 
 }  // namespace ek

@@ -17,6 +17,7 @@
 //   - launched lattice and upper grids (k_g_*), with the grids below in one workgroup
 //     (k_g_tail).
 // All sums run in a fixed order, so results are deterministic.
+#include "ek_device.h"
 #include "ek_gmg.h"
 
 #include <algorithm>
@@ -115,11 +116,15 @@ void gmg_hierarchy(const int (&dims)[3], const bool (&periodic)[3], GHier& H) {
     }
 }
 
-// Grids first .. last of a hierarchy as a workgroup holds them in LDS.
-GSub gmg_sub(const GHier& H, int first) {
+// Grids first .. last of a hierarchy as a workgroup holds them in LDS, with the axis tables
+// between them (from_lattice: also those from the lattice to the first of them).
+GSub gmg_sub(const GHier& H, int first, bool from_lattice) {
     GSub G{};
+    const int nl = (int)H.levels.size(), t0 = from_lattice ? first : first + 1;
+    G.pn0 = t0 < nl ? H.levels[t0].of[0] : (int)H.pn.size();
+    G.first0 = t0 < nl ? H.levels[t0].oc[0] : (int)H.first.size();
     int off = 0;
-    for (int l = first; l < (int)H.levels.size(); ++l) {
+    for (int l = first; l < nl; ++l) {
         const GLevelDesc& D = H.levels[l];
         GLds& L = G.L[G.nl++];
         const int e[3] = {D.d[D.lead], D.lead < 2 ? D.d[D.lead + 1] : 1, D.lead < 1 ? D.d[2] : 1};
@@ -132,12 +137,15 @@ GSub gmg_sub(const GHier& H, int first) {
         L.inv_ey = 1.0f / e[1];
         L.inv_nx = 1.0f / D.d[0];
         L.inv_ny = 1.0f / D.d[1];
-        for (int k = 0; k < 3; ++k) L.of[k] = D.of[k], L.oc[k] = D.oc[k];
+        for (int k = 0; k < 3; ++k) {
+            L.of[k] = l >= t0 ? D.of[k] - G.pn0 : 0;
+            L.oc[k] = l >= t0 ? D.oc[k] - G.first0 : 0;
+        }
         off += L.n;
     }
     G.cells = off;
-    G.npn = (int)H.pn.size();
-    G.nfirst = (int)H.first.size();
+    G.npn = (int)H.pn.size() - G.pn0;
+    G.nfirst = (int)H.first.size() - G.first0;
     return G;
 }
 
@@ -149,7 +157,18 @@ static size_t sub_bytes(const GSub& G, size_t scratch_cells) {
     return (size_t)G.cells * 64 + kDirect * kDirect * 8 + 64 * 8 + std::max((scratch_cells + 1) & ~(size_t)1, (size_t)(kDirect * kDirect)) * 8 + tabs + 32;
 }
 
-size_t gmg_tail_bytes(const GSub& G) { return sub_bytes(G, G.nl ? (size_t)G.L[0].n : 0); }
+static size_t tail_bytes(const GSub& G) { return sub_bytes(G, G.nl ? (size_t)G.L[0].n : 0); }
+
+// The first grid of the hierarchy from which on all of them fit one workgroup; -1: none.
+int gmg_tail_first(const GHier& H) {
+    const int nl = (int)H.levels.size();
+    if (nl == 0 || H.levels[nl - 1].n > (unsigned)kDirect) return -1;
+    int l = nl - 1;
+    while (l > 0 && (long long)H.levels[l - 1].n * 64 <= (long long)kGmgLds &&
+           tail_bytes(gmg_sub(H, l - 1, false)) <= kGmgLds)
+        --l;
+    return l;
+}
 
 bool gmg_small_fits(const GSub& G, unsigned ndomain) {
     return ndomain <= kSmallMost && sub_bytes(G, ndomain) + (size_t)ndomain * 8 <= kGmgLds;
@@ -202,8 +221,8 @@ __device__ __forceinline__ GArrays carve(char* lds, int& o, const GSub& G, int s
 
 __device__ __forceinline__ void load_tables(const GArrays& A, const GSub& G, const GTab& t, int tid, int nt) {
     for (int k = tid; k < G.npn; k += nt)
-        A.pw[k] = make_uint2(t.pn[k], __float_as_uint(t.w[k]));
-    for (int k = tid; k < G.nfirst; k += nt) A.first[k] = t.first[k];
+        A.pw[k] = make_uint2(t.pn[G.pn0 + k], __float_as_uint(t.w[G.pn0 + k]));
+    for (int k = tid; k < G.nfirst; k += nt) A.first[k] = t.first[G.first0 + k];
 }
 
 // The threads that work on a grid: the whole workgroup, or one wavefront of it (WAVE), which
@@ -619,7 +638,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
     ss = wg_sum(ss, A.sum, tid, nt);
     if (G.nl > 0) {
         lds_coarsen(
-            G.L[0], A, tab.ratio,
+            G.L[0], A, tab.ratio + G.first0,
             [&](int k, int x, int y, int z) -> double {
                 const int t = x + nx * (y + ny * z);
                 int j;
@@ -633,7 +652,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
             },
             tid, nt);
         __syncthreads();  // the last reads of eps, whose place the build reuses
-        lds_build<NT>(G, A, tab.ratio, A.res, tid);
+        lds_build<NT>(G, A, tab.ratio + G.first0, A.res, tid);
     }
 
     auto off_of = [&](int k) __attribute__((always_inline)) {
@@ -760,7 +779,304 @@ void launch_small_solve(const Scalars& S, const Fields<T>& F, const GSub& G, con
         go(k_small_solve<T, 4, 1024>, 1024);
 }
 
-template void launch_small_solve<float>(const Scalars&, const Fields<float>&, const GSub&, const GTab&, const SmallArgs&, hipStream_t);
-template void launch_small_solve<double>(const Scalars&, const Fields<double>&, const GSub&, const GTab&, const SmallArgs&, hipStream_t);
+// ------------------------------------------------------------------------------------
+// Launched grids: lattices above the single-workgroup size whose axes the V-cycle of
+// ek_kernels.hip cannot halve to the end.  The lattice is smoothed by its colour passes in
+// site order (three colours with an odd periodic axis) and the upper coarse grids by
+// k_mg_smooth on their compact axes; the grids that fit one workgroup run in k_g_tail.
+// These lattices took SOR before: 4 x 128 x 128 in FP64 319 sweeps a step, 2.9 ms.
+// ------------------------------------------------------------------------------------
+namespace {
+
+__device__ __forceinline__ double* coef_of(const MGLevel& M, int lead, int k) {
+    const int s = k - lead;
+    return s == 0 ? M.ax : (s == 1 ? M.ay : M.az);
+}
+
+struct Box {
+    int lo[3], hi[3];
+};
+
+// Coordinates of cell t of a grid, and its children.
+__device__ __forceinline__ void cell_of(const GTrans& C, unsigned t, int& I, int& J, int& K) {
+    const unsigned r = div_exact(t, C.inv_nx);
+    I = (int)(t - r * (unsigned)C.d[0]);
+    K = (int)div_exact(r, C.inv_ny);
+    J = (int)(r - (unsigned)K * (unsigned)C.d[1]);
+}
+
+__device__ __forceinline__ Box children(const GTrans& C, const GTab& t, int I, int J, int K) {
+    Box b;
+    b.lo[0] = t.first[C.oc[0] + I], b.hi[0] = t.first[C.oc[0] + I + 1];
+    b.lo[1] = t.first[C.oc[1] + J], b.hi[1] = t.first[C.oc[1] + J + 1];
+    b.lo[2] = t.first[C.oc[2] + K], b.hi[2] = t.first[C.oc[2] + K + 1];
+    return b;
+}
+
+// Stores the face coefficients of coarse cell t from the fine faces face(k, x, y, z).
+template <typename FaceFn>
+__device__ __forceinline__ void coarsen_cell(const GTrans& C, const MGLevel& M, const GTab& tab, unsigned t,
+                                             FaceFn&& face) {
+    int I, J, K;
+    cell_of(C, t, I, J, K);
+    const Box b = children(C, tab, I, J, K);
+    double s[3] = {0.0, 0.0, 0.0};
+    const int n0 = b.hi[0] - b.lo[0], n1 = b.hi[1] - b.lo[1], n2 = b.hi[2] - b.lo[2];
+    if (C.d[0] > 1) s[0] = sum_box(1, n1, n2, [&](int, int y, int z) { return face(0, b.hi[0] - 1, b.lo[1] + y, b.lo[2] + z); });
+    if (C.d[1] > 1) s[1] = sum_box(n0, 1, n2, [&](int x, int, int z) { return face(1, b.lo[0] + x, b.hi[1] - 1, b.lo[2] + z); });
+    if (C.d[2] > 1) s[2] = sum_box(n0, n1, 1, [&](int x, int y, int) { return face(2, b.lo[0] + x, b.lo[1] + y, b.hi[2] - 1); });
+    const double c0 = s[0] * (double)tab.ratio[C.oc[0] + I], c1 = s[1] * (double)tab.ratio[C.oc[1] + J],
+                 c2 = s[2] * (double)tab.ratio[C.oc[2] + K];
+    M.ax[t] = C.lead == 0 ? c0 : (C.lead == 1 ? c1 : c2);
+    M.ay[t] = C.lead == 0 ? c1 : (C.lead == 1 ? c2 : 0.0);
+    M.az[t] = C.lead == 0 ? c2 : 0.0;
+}
+
+// Row of cell i of a grid in its compact axes.
+__device__ __forceinline__ void grid_row(const MGLevel& M, unsigned i, double& diag, double& off) {
+    int x, y, z;
+    level_xyz(i, M, x, y, z);
+    const unsigned ex = (unsigned)M.nx, exy = ex * (unsigned)M.ny;
+    const unsigned xm = x == 0 ? i + ex - 1 : i - 1, xp = x == M.nx - 1 ? i - (ex - 1) : i + 1;
+    const unsigned ym = y == 0 ? i + exy - ex : i - ex, yp = y == M.ny - 1 ? i - (exy - ex) : i + ex;
+    const unsigned zm = z == 0 ? i + exy * (unsigned)(M.nz - 1) : i - exy,
+                   zp = z == M.nz - 1 ? i - exy * (unsigned)(M.nz - 1) : i + exy;
+    const double a0 = M.ax[i], a1 = M.ax[xm], b0 = M.ay[i], b1 = M.ay[ym], c0 = M.az[i], c1 = M.az[zm];
+    diag = a0 + a1 + b0 + b1 + c0 + c1;
+    off = a0 * M.phi[xp] + a1 * M.phi[xm] + b0 * M.phi[yp] + b1 * M.phi[ym] + c0 * M.phi[zp] + c1 * M.phi[zm];
+}
+
+// Right-hand side of coarse cell t and the start of its correction: zero, or with
+// red_omega > 0 on red cells the first red pass of the pre-smoothing, which from a zero
+// correction is omega s / diag.
+__device__ __forceinline__ void coarse_begin(const MGLevel& M, unsigned t, double s, double red_omega) {
+    double v = 0.0;
+    if (red_omega > 0.0) {
+        int x, y, z;
+        level_xyz(t, M, x, y, z);
+        if (((x + y + z) & 1) == 0) {
+            const unsigned ex = (unsigned)M.nx, exy = ex * (unsigned)M.ny;
+            const unsigned xm = x == 0 ? t + ex - 1 : t - 1, ym = y == 0 ? t + exy - ex : t - ex,
+                           zm = z == 0 ? t + exy * (unsigned)(M.nz - 1) : t - exy;
+            const double d = M.ax[t] + M.ax[xm] + M.ay[t] + M.ay[ym] + M.az[t] + M.az[zm];
+            if (d > 0.0) v = red_omega * (s / d);
+        }
+    }
+    M.s[t] = s;
+    M.phi[t] = v;
+}
+
+// Sum over the children of coarse cell t by eight lanes, lane (a, b, c) taking every other
+// child along each axis; in lane 0.
+template <typename Fn>
+__device__ __forceinline__ double restrict_cell(const GTrans& C, const GTab& tab, unsigned t, int lane, Fn&& residual) {
+    int I, J, K;
+    cell_of(C, t, I, J, K);
+    const Box b = children(C, tab, I, J, K);
+    double s = 0.0;
+    for (int z = b.lo[2] + (lane >> 2); z < b.hi[2]; z += 2)
+        for (int y = b.lo[1] + ((lane >> 1) & 1); y < b.hi[1]; y += 2)
+            for (int x = b.lo[0] + (lane & 1); x < b.hi[0]; x += 2) s += residual(x, y, z);
+#pragma unroll
+    for (int m = 4; m > 0; m >>= 1) s += __shfl_down(s, m, 8);
+    return s;
+}
+
+__device__ __forceinline__ double interp_at(const GTrans& C, const MGLevel& M, const GTab& t, int x, int y, int z) {
+    const uint32_t px = t.pn[C.of[0] + x], py = t.pn[C.of[1] + y], pz = t.pn[C.of[2] + z];
+    const double wx = t.w[C.of[0] + x], wy = t.w[C.of[1] + y], wz = t.w[C.of[2] + z];
+    const unsigned x0 = px & 0xffffu, x1 = px >> 16, cx = (unsigned)C.d[0], cxy = cx * (unsigned)C.d[1];
+    const unsigned y0 = cx * (py & 0xffffu), y1 = cx * (py >> 16), z0 = cxy * (pz & 0xffffu), z1 = cxy * (pz >> 16);
+    const double* p = M.phi;
+    auto line = [&](unsigned o) { return p[o + x0] + wx * (p[o + x1] - p[o + x0]); };
+    const double a = line(y0 + z0), b = line(y1 + z0), c = line(y0 + z1), d = line(y1 + z1);
+    const double lo = a + wy * (b - a), hi = c + wy * (d - c);
+    return lo + wz * (hi - lo);
+}
+
+// Domain site of lattice coordinates (z counted from the first domain layer).
+__device__ __forceinline__ unsigned domain_site(const Scalars& S, int x, int y, int z) {
+    return (unsigned)x + (unsigned)S.nx * ((unsigned)y + (unsigned)S.ny * (unsigned)(z + S.z0));
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_g_coarsen0(Scalars S, Fields<T> F, GTrans C, MGLevel M, GTab tab) {
+    const unsigned t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= C.n) return;
+    const int nzd = S.z1 - S.z0 + 1;
+    coarsen_cell(C, M, tab, t, [&](int k, int x, int y, int z) {
+        const int x2 = k == 0 ? (x + 1 == S.nx ? 0 : x + 1) : x, y2 = k == 1 ? (y + 1 == S.ny ? 0 : y + 1) : y,
+                  z2 = k == 2 ? (z + 1 == nzd ? 0 : z + 1) : z;
+        return 0.5 * ((double)F.eps[domain_site(S, x, y, z)] + (double)F.eps[domain_site(S, x2, y2, z2)]);
+    });
+}
+
+__global__ __launch_bounds__(kBlock) void k_g_coarsen(GTrans Cf, MGLevel Mf, GTrans C, MGLevel M, GTab tab) {
+    const unsigned t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= C.n) return;
+    coarsen_cell(C, M, tab, t, [&](int k, int x, int y, int z) {
+        return coef_of(Mf, Cf.lead, k)[(unsigned)x + (unsigned)Cf.d[0] * ((unsigned)y + (unsigned)Cf.d[1] * (unsigned)z)];
+    });
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_g_restrict0(Scalars S, Fields<T> F, GTrans C, MGLevel M, GTab tab,
+                                                        double red_omega) {
+    const unsigned u = blockIdx.x * kBlock + threadIdx.x, t = u >> 3;
+    if (t >= C.n) return;  // groups of eight lanes leave together
+    const double mean = F.scal[0];
+    const int nzd = S.z1 - S.z0 + 1;
+    const double s = restrict_cell(C, tab, t, (int)(u & 7u), [&](int x, int y, int z) {
+        const unsigned i = domain_site(S, x, y, z), nx = (unsigned)S.nx, nxy = (unsigned)S.nxy;
+        const unsigned xa = x == 0 ? i + nx - 1 : i - 1, xb = x == S.nx - 1 ? i - (nx - 1) : i + 1;
+        const unsigned ya = y == 0 ? i + nxy - nx : i - nx, yb = y == S.ny - 1 ? i - (nxy - nx) : i + nx;
+        const unsigned za = z == 0 ? i + nxy * (unsigned)(nzd - 1) : i - nxy,
+                       zb = z == nzd - 1 ? i - nxy * (unsigned)(nzd - 1) : i + nxy;
+        const bool ony = S.ny > 1, lo = nzd > 1 && !(S.walls && z == 0), hi = nzd > 1 && !(S.walls && z == nzd - 1);
+        const double ei = F.eps[i], p = F.phi[i];
+        const double fxm = 0.5 * (ei + (double)F.eps[xa]), fxp = 0.5 * (ei + (double)F.eps[xb]);
+        const double fym = ony ? 0.5 * (ei + (double)F.eps[ya]) : 0.0, fyp = ony ? 0.5 * (ei + (double)F.eps[yb]) : 0.0;
+        const double fzm = lo ? 0.5 * (ei + (double)F.eps[za]) : 0.0, fzp = hi ? 0.5 * (ei + (double)F.eps[zb]) : 0.0;
+        double src = (double)F.q[i];
+        if (S.walls && z == 0) src += S.sigma0;
+        if (S.walls && z == nzd - 1) src += S.sigma1;
+        if (S.polar) src -= S.E_ext[0] * (fxp - fxm) + S.E_ext[1] * (fyp - fym) + S.E_ext[2] * (fzp - fzm);
+        return (src - mean) + fxp * (F.phi[xb] - p) + fxm * (F.phi[xa] - p) + fyp * (F.phi[yb] - p) +
+               fym * (F.phi[ya] - p) + fzp * (F.phi[zb] - p) + fzm * (F.phi[za] - p);
+    });
+    if ((u & 7u) == 0) coarse_begin(M, t, s, red_omega);
+}
+
+__global__ __launch_bounds__(kBlock) void k_g_restrict(GTrans Cf, MGLevel Mf, GTrans C, MGLevel M, GTab tab,
+                                                       double red_omega) {
+    const unsigned u = blockIdx.x * kBlock + threadIdx.x, t = u >> 3;
+    if (t >= C.n) return;
+    const double s = restrict_cell(C, tab, t, (int)(u & 7u), [&](int x, int y, int z) {
+        const unsigned i = (unsigned)x + (unsigned)Cf.d[0] * ((unsigned)y + (unsigned)Cf.d[1] * (unsigned)z);
+        double diag, off;
+        grid_row(Mf, i, diag, off);
+        return Mf.s[i] + off - diag * Mf.phi[i];
+    });
+    if ((u & 7u) == 0) coarse_begin(M, t, s, red_omega);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_g_prolong0(Scalars S, Fields<T> F, GTrans C, MGLevel M, GTab tab) {
+    const unsigned t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= S.ndomain) return;
+    const unsigned i = t + (unsigned)S.z0 * (unsigned)S.nxy;
+    int x, y, z;
+    site_xyz(i, S, x, y, z);
+    F.phi[i] += interp_at(C, M, tab, x, y, z - S.z0);
+}
+
+__global__ __launch_bounds__(kBlock) void k_g_prolong(GTrans Cf, MGLevel Mf, GTrans C, MGLevel M, GTab tab) {
+    const unsigned t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= Cf.n) return;
+    int x, y, z;
+    cell_of(Cf, t, x, y, z);
+    Mf.phi[t] += interp_at(C, M, tab, x, y, z);
+}
+
+constexpr int kTailGThreads = 512;
+
+// Rows of the grids that k_g_tail holds and the coarsest one's inverse, once per solve, from
+// the first of them's coefficients (M); kept in `rows` as k_g_tail loads them.
+__global__ __launch_bounds__(kTailGThreads) void k_g_tail_build(GSub G, GTab tab, MGLevel M, uint4* rows) {
+    extern __shared__ __align__(16) char lds_raw[];
+    const int tid = threadIdx.x;
+    constexpr int nt = kTailGThreads;
+    int used;
+    const GArrays A = carve(lds_raw, used, G, G.L[0].n);
+    load_tables(A, G, tab, tid, nt);
+    const GLds& L = G.L[0];
+    const float inv_ex = 1.0f / L.ex;
+    for (int i = tid; i < L.n; i += nt) {
+        const int row = fdiv(i, inv_ex), x = i - row * L.ex, z = fdiv(row, L.inv_ey), y = row - z * L.ey;
+        const int e = lds_place(L, i, x, y, z);
+        A.ca[e].x = (float)M.ax[i];
+        A.ca[e].z = (float)M.ay[i];
+        A.cb[e].x = (float)M.az[i];
+    }
+    __syncthreads();
+    lds_build<nt>(G, A, tab.ratio + G.first0, A.res, tid);
+    const uint4* all = A.nb;  // nb, ca, cb and inv lie one after another but for phi and rhs
+    for (int k = tid; k < 3 * G.cells; k += nt) rows[k] = all[k];
+    double* inv = (double*)(rows + 3 * G.cells);
+    for (int k = tid; k < kDirect * kDirect; k += nt) inv[k] = A.inv[k];
+}
+
+// One V-cycle on the grids of G for the right-hand side M.s; the correction goes to M.phi.
+__global__ __launch_bounds__(kTailGThreads) void k_g_tail(GSub G, GTab tab, MGLevel M, const uint4* rows, GShape sh) {
+    extern __shared__ __align__(16) char lds_raw[];
+    const int tid = threadIdx.x;
+    constexpr int nt = kTailGThreads;
+    int used;
+    const GArrays A = carve(lds_raw, used, G, G.L[0].n);
+    uint4* all = A.nb;
+    for (int k = tid; k < 3 * G.cells; k += nt) all[k] = rows[k];
+    const double* inv = (const double*)(rows + 3 * G.cells);
+    for (int k = tid; k < kDirect * kDirect; k += nt) A.inv[k] = inv[k];
+    load_tables(A, G, tab, tid, nt);
+    for (int i = tid; i < G.L[0].n; i += nt) {
+        A.rhs[i] = M.s[i];
+        A.phi[i] = 0.0;
+    }
+    __syncthreads();
+    lds_vcycle(G, A, sh, tid, nt);
+    for (int i = tid; i < G.L[0].n; i += nt) M.phi[i] = A.phi[i];
+}
+
+unsigned blocks_of(unsigned n) { return (n + kBlock - 1) / kBlock; }
+
+}  // namespace
+
+size_t gmg_rows_bytes(const GSub& G) { return (size_t)G.cells * 48 + kDirect * kDirect * 8; }
+
+template <typename T>
+void launch_g_coarsen0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                       hipStream_t st) {
+    hipLaunchKernelGGL(k_g_coarsen0<T>, dim3(blocks_of(C.n)), dim3(kBlock), 0, st, S, F, C, M, t);
+}
+void launch_g_coarsen(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_g_coarsen, dim3(blocks_of(C.n)), dim3(kBlock), 0, st, Cf, Mf, C, M, t);
+}
+template <typename T>
+void launch_g_restrict0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                        double red_omega, hipStream_t st) {
+    hipLaunchKernelGGL(k_g_restrict0<T>, dim3(blocks_of(8 * C.n)), dim3(kBlock), 0, st, S, F, C, M, t, red_omega);
+}
+void launch_g_restrict(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                       double red_omega, hipStream_t st) {
+    hipLaunchKernelGGL(k_g_restrict, dim3(blocks_of(8 * C.n)), dim3(kBlock), 0, st, Cf, Mf, C, M, t, red_omega);
+}
+template <typename T>
+void launch_g_prolong0(const Scalars& S, const Fields<T>& F, const GTrans& C, const MGLevel& M, const GTab& t,
+                       hipStream_t st) {
+    hipLaunchKernelGGL(k_g_prolong0<T>, dim3(blocks_of(S.ndomain)), dim3(kBlock), 0, st, S, F, C, M, t);
+}
+void launch_g_prolong(const GTrans& Cf, const MGLevel& Mf, const GTrans& C, const MGLevel& M, const GTab& t,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_g_prolong, dim3(blocks_of(Cf.n)), dim3(kBlock), 0, st, Cf, Mf, C, M, t);
+}
+void launch_g_tail_build(const GSub& G, const GTab& t, const MGLevel& M, void* rows, hipStream_t st) {
+    hipLaunchKernelGGL(k_g_tail_build, dim3(1), dim3(kTailGThreads), tail_bytes(G), st, G, t, M, (uint4*)rows);
+}
+void launch_g_tail(const GSub& G, const GTab& t, const MGLevel& M, const void* rows, const GShape& sh, hipStream_t st) {
+    hipLaunchKernelGGL(k_g_tail, dim3(1), dim3(kTailGThreads), tail_bytes(G), st, G, t, M, (const uint4*)rows, sh);
+}
+
+#define EK_GMG_INST(T)                                                                                                 \
+    template void launch_small_solve<T>(const Scalars&, const Fields<T>&, const GSub&, const GTab&, const SmallArgs&,  \
+                                        hipStream_t);                                                                  \
+    template void launch_g_coarsen0<T>(const Scalars&, const Fields<T>&, const GTrans&, const MGLevel&, const GTab&,   \
+                                       hipStream_t);                                                                   \
+    template void launch_g_restrict0<T>(const Scalars&, const Fields<T>&, const GTrans&, const MGLevel&, const GTab&,  \
+                                        double, hipStream_t);                                                          \
+    template void launch_g_prolong0<T>(const Scalars&, const Fields<T>&, const GTrans&, const MGLevel&, const GTab&,   \
+                                       hipStream_t);
+EK_GMG_INST(float)
+EK_GMG_INST(double)
 
 }  // namespace ek
