@@ -558,10 +558,10 @@ static void cycles_forget(ek_ctx* c) {
 // F in site order (split false) and pack: the kernel also fills c->phis, c->qs.
 template <typename T>
 static ek_status check_residual(ek_ctx* c, const Fields<T>& F, bool split, bool pack, double& rr, double& ss) {
-    const unsigned nres = residual_blocks(c->N);
+    const unsigned nres = residual_blocks(c->S);
     {
         EK_KT(EK_K_RESIDUAL);
-        launch_residual<T>(c->S, F, nres, split, pack ? c->phis : nullptr, pack ? (T*)c->qs : nullptr, c->st);
+        launch_residual<T>(c->S, F, split, pack ? c->phis : nullptr, pack ? (T*)c->qs : nullptr, c->st);
     }
     {
         EK_KT(EK_K_REDUCE);
@@ -655,12 +655,12 @@ static void vcycle(ek_ctx* c, const Fields<T>& F0, bool split) {
             // pass reads the interpolated black values from c->blk
             {
                 EK_KT(EK_K_PROLONG_RED_FINE);
-                launch_mg_prolong_red_fine<T>(c->S, F, c->mg[0], c->mg_omega, c->blk, c->st);
+                launch_prolong_red_col<T>(c->S, F, c->mg[0], c->mg_omega, c->blk, c->st);
             }
             Timer tm(c, EK_T_SMOOTH, 2 * post - 1);
             {
                 EK_KT(EK_K_SOR_BLACK_FROM);
-                launch_sor_black_from<T>(c->S, F, c->mg_omega, c->blk, c->st);
+                launch_sor_col<T>(c->S, F, 1, c->mg_omega, c->blk, c->st);
             }
             for (int s = 1; s < post; ++s) smooth(0);
             continue;
@@ -877,10 +877,10 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
         // reduced on the device, where ek_observables reads them (and the largest since its
         // last call).  The step is then one stream of launches with no synchronisation.
         const int k = c->fixed_cycles;
-        const unsigned nres = residual_blocks(c->N);
+        const unsigned nres = residual_blocks(c->S);
         {
             EK_KT(EK_K_RESIDUAL);
-            launch_residual<T>(c->S, F, nres, false, split ? c->phis : nullptr, split ? (T*)c->qs : nullptr, c->st);
+            launch_residual<T>(c->S, F, false, split ? c->phis : nullptr, split ? (T*)c->qs : nullptr, c->st);
         }
         {
             EK_KT(EK_K_REDUCE);
@@ -893,7 +893,7 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
         }
         {
             EK_KT(EK_K_RESIDUAL);
-            launch_residual<T>(c->S, FS, nres, split, nullptr, nullptr, c->st);
+            launch_residual<T>(c->S, FS, split, nullptr, nullptr, c->st);
         }
         {
             EK_KT(EK_K_REDUCE);
@@ -926,10 +926,10 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
     int it = 0;
     bool built = false;
     if (k0 > 0) {
-        const unsigned nres = residual_blocks(c->N);
+        const unsigned nres = residual_blocks(c->S);
         {
             EK_KT(EK_K_RESIDUAL);
-            launch_residual<T>(c->S, F, nres, false, split ? c->phis : nullptr, split ? (T*)c->qs : nullptr, c->st);
+            launch_residual<T>(c->S, F, false, split ? c->phis : nullptr, split ? (T*)c->qs : nullptr, c->st);
         }
         {
             EK_KT(EK_K_REDUCE);
@@ -945,7 +945,7 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
         it = k0;
         {
             EK_KT(EK_K_RESIDUAL);
-            launch_residual<T>(c->S, FS, nres, split, nullptr, nullptr, c->st);
+            launch_residual<T>(c->S, FS, split, nullptr, nullptr, c->st);
         }
         {
             EK_KT(EK_K_REDUCE);

@@ -102,7 +102,7 @@ struct MGLevel {
 };
 
 unsigned site_blocks(unsigned n);
-unsigned residual_blocks(unsigned n);  // workgroups of the residual kernel for n sites
+unsigned residual_blocks(const Scalars& S);  // workgroups of the residual kernel
 
 // Reverse-mode (adjoint) fields of a periodic FP64 context for one reverse step: the
 // sensitivities of a scalar objective L to the step's inputs and intermediates.  All
@@ -174,14 +174,22 @@ void launch_mg_restrict_fine(const Scalars& S, const Fields<T>& F, const MGLevel
 void launch_mg_restrict(const MGLevel& f, const MGLevel& c, double red_omega, hipStream_t st);
 template <typename T>
 void launch_mg_prolong_fine(const Scalars& S, const Fields<T>& F, const MGLevel& c, bool split, hipStream_t st);
-// Colour-split fields: interpolation onto the lattice with the first red pass of the
-// post-smoothing; the interpolated black values go to blk (N/2 doubles), which the black
-// pass launch_sor_black_from reads as the black sites' current values.
+// The column kernels (ek_columns.hip), where columns_fit(S): a colour pass over colour-split
+// fields, relaxed from cur (null: in place), and the residual sums of launch_residual.
+bool columns_fit(const Scalars& S);
+unsigned residual_col_blocks(const Scalars& S);
 template <typename T>
-void launch_mg_prolong_red_fine(const Scalars& S, const Fields<T>& F, const MGLevel& c, double omega, double* blk,
-                                hipStream_t st);
+void launch_sor_col(const Scalars& S, const Fields<T>& F, int color, double omega, const double* cur, hipStream_t st);
 template <typename T>
-void launch_sor_black_from(const Scalars& S, const Fields<T>& F, double omega, const double* blk, hipStream_t st);
+void launch_residual_col(const Scalars& S, const Fields<T>& F, bool split, double* phis, T* qs, hipStream_t st);
+// Colour-split fields: the fine restriction, and the interpolation onto the lattice with the first
+// red pass of the post-smoothing; the interpolated black values go to blk (N/2 doubles), from
+// which the black pass relaxes.
+template <typename T>
+void launch_restrict_col(const Scalars& S, const Fields<T>& F, const MGLevel& c, double red_omega, hipStream_t st);
+template <typename T>
+void launch_prolong_red_col(const Scalars& S, const Fields<T>& F, const MGLevel& c, double omega, double* blk,
+                            hipStream_t st);
 // One whole red-black sweep in one pass, colour-split fields from pin to pout (F.phi is not
 // read); only where sor_rb_fits(S).
 bool sor_rb_fits(const Scalars& S);
@@ -200,8 +208,7 @@ template <typename T>
 void launch_sor(const Scalars& S, const Fields<T>& F, int color, double omega, bool split, hipStream_t st);
 // From site-order fields (split false) with phis, qs non-null: also writes their colour-split copies
 template <typename T>
-void launch_residual(const Scalars& S, const Fields<T>& F, unsigned nblk, bool split, double* phis, T* qs,
-                     hipStream_t st);
+void launch_residual(const Scalars& S, const Fields<T>& F, bool split, double* phis, T* qs, hipStream_t st);
 void launch_reduce(const double* red, unsigned nblk, int nvals, const int* is_max, double* out, hipStream_t st);
 // gauge mean(phi) = 0 (phi = 0 when zero != 0) and the wall layers of the potential
 // split_src: the colour-split solved potential, or null to gauge F.phi in place

@@ -19,6 +19,7 @@
 // in that XCD's L2).  Reductions are wave64 shuffles + LDS + a fixed-order final pass,
 // so results are deterministic run to run.
 #include "ek_device.h"
+#include "ek_poisson.h"
 
 namespace ek {
 
@@ -441,96 +442,15 @@ void launch_source_mean(const Scalars& S, double* red, unsigned nblk, double* sc
 // contribute nothing, so they are skipped.
 // ------------------------------------------------------------------------------------
 //
-// Inside a multigrid solve the lattice potential and charge can be held colour-split (SP):
-// the sites of colour (x + y + z) % 2 = 1 follow those of colour 0, each colour in site
-// order, so a colour pass reads and writes whole cache lines of its own colour.  Axes are
-// even there, site i of colour c sits at c N/2 + i/2, and every neighbour has the other
-// colour.  The permittivity stays in site order.
-template <bool SP>
-__device__ __forceinline__ unsigned cidx(const Scalars& S, unsigned i, int color) {
-    return SP ? (color ? (S.N >> 1) : 0u) + (i >> 1) : i;
-}
-
-// The row with the neighbour potentials supplied by pv(j, colour, ox, oy, oz) for the
-// neighbour j at offset (ox, oy, oz); poisson_row reads them from F.phi.  Evaluated
-// without multiply-add contraction, so that callers supplying the neighbour values
-// differently (loaded, or interpolated on the fly) round the row identically.  Every
-// operand is fetched before the arithmetic: the faces that an axis of length 1 or a wall
-// leaves out are fetched too (their indices are lattice sites: the site itself, or a wall
-// layer) and then not used, so the loads carry no branches and issue together.
-// The permittivities come from ev(j, ox, oy, oz) the same way and the charge from qv()
-// (poisson_row_v: from F.eps and F.q).
-template <typename T, bool SP, typename PV, typename EV, typename QV>
-__device__ __forceinline__ void poisson_row_ve(unsigned i, int x, int y, int z, const Scalars& S, const Fields<T>& F,
-                                               PV&& pv, EV&& ev, QV&& qv, double& diag, double& offsum, double& src) {
-#pragma clang fp contract(off)
-    const int own = SP ? ((x + y + z) & 1) : 0, nb = own ^ 1;
-    const unsigned xa = i + (x == 0 ? S.nx - 1 : -1), xb = i + (x == S.nx - 1 ? -(S.nx - 1) : 1);
-    const unsigned ya = i + (y == 0 ? (S.ny - 1) * S.nx : -S.nx), yb = i + (y == S.ny - 1 ? -(S.ny - 1) * S.nx : S.nx);
-    const unsigned za = i + (z == 0 ? (S.nz - 1) * S.nxy : -S.nxy), zb = i + (z == S.nz - 1 ? -(S.nz - 1) * S.nxy : S.nxy);
-    const double ei = ev(i, 0, 0, 0);
-    const double exa = ev(xa, -1, 0, 0), exb = ev(xb, 1, 0, 0), eya = ev(ya, 0, -1, 0), eyb = ev(yb, 0, 1, 0),
-                 eza = ev(za, 0, 0, -1), ezb = ev(zb, 0, 0, 1);
-    const double pxa = pv(xa, nb, -1, 0, 0), pxb = pv(xb, nb, 1, 0, 0), pya = pv(ya, nb, 0, -1, 0),
-                 pyb = pv(yb, nb, 0, 1, 0), pza = pv(za, nb, 0, 0, -1), pzb = pv(zb, nb, 0, 0, 1);
-    double s = qv();
-    diag = 0.0;
-    offsum = 0.0;
-    double pol = 0.0;  // sum over the faces of eps_f (E_ext . c_d): the polarisation source
-    // A face that is left out (an axis of length 1, a wall) is taken with a zero
-    // coefficient: adding +0 leaves every sum as it is, and the row has no branches, so the
-    // loads of consecutive rows can overlap.
-    {
-        const bool on = S.nx > 1;
-        const double ea = on ? 0.5 * (ei + exa) : 0.0, eb = on ? 0.5 * (ei + exb) : 0.0;
-        diag += ea + eb;
-        offsum += ea * pxa + eb * pxb;
-        pol += S.E_ext[0] * (eb - ea);
-    }
-    {
-        const bool on = S.ny > 1;
-        const double ea = on ? 0.5 * (ei + eya) : 0.0, eb = on ? 0.5 * (ei + eyb) : 0.0;
-        diag += ea + eb;
-        offsum += ea * pya + eb * pyb;
-        pol += S.E_ext[1] * (eb - ea);
-    }
-    {
-        const bool lo = S.nz > 1 && !(S.walls && z == S.z0), hi = S.nz > 1 && !(S.walls && z == S.z1);
-        const double ea = lo ? 0.5 * (ei + eza) : 0.0, eb = hi ? 0.5 * (ei + ezb) : 0.0;
-        diag += ea;
-        offsum += ea * pza;
-        pol -= S.E_ext[2] * ea;
-        diag += eb;
-        offsum += eb * pzb;
-        pol += S.E_ext[2] * eb;
-    }
-    if (S.walls && z == S.z0) s += S.sigma0;
-    if (S.walls && z == S.z1) s += S.sigma1;
-    if (S.polar) s -= pol;
-    src = s - F.scal[0];
-}
-
-template <typename T, bool SP, typename PV>
-__device__ __forceinline__ void poisson_row_v(unsigned i, int x, int y, int z, const Scalars& S, const Fields<T>& F,
-                                              PV&& pv, double& diag, double& offsum, double& src) {
-    poisson_row_ve<T, SP>(
-        i, x, y, z, S, F, pv, [&](unsigned j, int, int, int) { return (double)F.eps[j]; },
-        [&]() { return (double)F.q[cidx<SP>(S, i, SP ? ((x + y + z) & 1) : 0)]; }, diag, offsum, src);
-}
-
-template <typename T, bool SP = false>
+// The row, its colour-split indexing and the update are in ek_poisson.h, shared with the column
+// kernels (ek_columns.hip), which take the lattice passes of colour-split fields.
+template <typename T>
 __device__ __forceinline__ void poisson_row(unsigned i, int x, int y, int z, const Scalars& S, const Fields<T>& F,
                                             double& diag, double& offsum, double& src) {
-    poisson_row_v<T, SP>(
-        i, x, y, z, S, F, [&](unsigned j, int c, int, int, int) { return F.phi[cidx<SP>(S, j, c)]; }, diag, offsum,
-        src);
-}
-
-// Over-relaxed Gauss-Seidel update, without multiply-add contraction so that every kernel
-// that applies it (separate or fused with the interpolation) rounds it the same way.
-__device__ __forceinline__ double sor_update(double p, double gs, double omega) {
-#pragma clang fp contract(off)
-    return p + omega * (gs - p);
+    poisson_row_ve<T, false>(
+        i, x, y, z, S, F, [&](unsigned j, int, int, int, int) { return F.phi[j]; },
+        [&](unsigned j, int, int, int) { return (double)F.eps[j]; }, [&]() { return (double)F.q[i]; }, F.scal[0], diag,
+        offsum, src);
 }
 
 // Colour of a site when a periodic y or z axis has odd length L >= 3.  On such an axis the
@@ -547,23 +467,20 @@ __device__ __forceinline__ int color3(const Scalars& S, int x, int y, int z) {
 
 // One colour of a Gauss-Seidel sweep.  Two colours (the usual red-black ordering): thread
 // -> site of that colour ((x + y + z) % 2 == color).  Three colours: thread -> domain site,
-// threads of other colours return.  sor_site computes the new value and where it goes;
-// with OWN the site's current value is read from own[i / 2] (the black values left by the
-// fused interpolation and red pass) instead of F.phi.
-template <typename T, bool SP = false, bool OWN = false>
-__device__ __forceinline__ bool sor_site(const Scalars& S, const Fields<T>& F, unsigned t, int color, double omega,
-                                         unsigned& o, double& v, const double* own = nullptr) {
+// threads of other colours return.
+template <typename T>
+__device__ __forceinline__ void sor_body(const Scalars& S, const Fields<T>& F, unsigned t, int color, double omega) {
     unsigned i;
     int x, y, z;
     if (S.ncolor == 3) {
-        if (t >= S.ndomain) return false;
+        if (t >= S.ndomain) return;
         i = t + (unsigned)S.z0 * (unsigned)S.nxy;
         site_xyz(i, S, x, y, z);
-        if (color3(S, x, y, z) != color) return false;
+        if (color3(S, x, y, z) != color) return;
     } else {
         const unsigned half = (unsigned)(S.nx >> 1);
         const unsigned rows = (unsigned)S.ny * (unsigned)(S.z1 - S.z0 + 1);
-        if (t >= half * rows) return false;
+        if (t >= half * rows) return;
         const unsigned row = div_exact(t, S.inv_hx), m = t - row * half;
         const unsigned zr = div_exact(row, S.inv_ny);
         y = (int)(row - zr * (unsigned)S.ny);
@@ -571,45 +488,14 @@ __device__ __forceinline__ bool sor_site(const Scalars& S, const Fields<T>& F, u
         x = 2 * m + ((color + y + z) & 1);
         i = x + S.nx * (y + S.ny * z);
     }
-    o = cidx<SP>(S, i, color);
-    const double p = OWN ? own[i >> 1] : F.phi[o];
     double diag, offsum, src;
-    poisson_row<T, SP>(i, x, y, z, S, F, diag, offsum, src);
-    if (diag <= 0.0) {  // an isolated site keeps its value (with OWN: the one in own)
-        if (!OWN) return false;
-        v = p;
-        return true;
-    }
-    const double gs = (offsum + src) / diag;
-    v = sor_update(p, gs, omega);
-    return true;
+    poisson_row<T>(i, x, y, z, S, F, diag, offsum, src);
+    if (diag > 0.0) F.phi[i] = sor_update(F.phi[i], diag, offsum, src, omega);  // an isolated site keeps its value
 }
 
-template <typename T, bool SP = false>
-__device__ __forceinline__ void sor_body(const Scalars& S, const Fields<T>& F, unsigned t, int color, double omega) {
-    unsigned o;
-    double v;
-    if (sor_site<T, SP>(S, F, t, color, omega, o, v)) F.phi[o] = v;
-}
-
-template <typename T, bool SP>
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_sor(Scalars S, Fields<T> F, int color, double omega) {
-    sor_body<T, SP>(S, F, xcd_linear(), color, omega);
-}
-
-// The black pass after k_mg_prolong_red_fine: own values from blk.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_sor_black_from(Scalars S, Fields<T> F, double omega,
-                                                           const double* __restrict__ blk) {
-    unsigned o;
-    double v;
-    if (sor_site<T, true, true>(S, F, xcd_linear(), 1, omega, o, v, blk)) F.phi[o] = v;
-}
-
-template <typename T>
-void launch_sor_black_from(const Scalars& S, const Fields<T>& F, double omega, const double* blk, hipStream_t st) {
-    const unsigned n = (unsigned)(S.nx / 2) * S.ny * (S.z1 - S.z0 + 1);
-    hipLaunchKernelGGL(k_sor_black_from<T>, dim3(site_blocks(n)), dim3(kBlock), 0, st, S, F, omega, blk);
+    sor_body<T>(S, F, xcd_linear(), color, omega);
 }
 
 // One whole red-black sweep in one pass over colour-split fields, from pin to pout.  A
@@ -733,9 +619,9 @@ __global__ __launch_bounds__(kBlock) void k_sor_rb(Scalars S, Fields<T> F, const
         poisson_row_ve<T, true>(
             0u, x, y, zz, S, F, [&](unsigned, int, int ox, int oy, int oz) { return v[s3(k + oz)][p + ox + oy * kRbLX]; },
             [&](unsigned, int ox, int oy, int oz) { return (double)seps[s4(k + oz)][p + ox + oy * kRbLX]; },
-            [&]() { return (double)q; }, diag, offsum, src);
+            [&]() { return (double)q; }, F.scal[0], diag, offsum, src);
         const double old = sphi[s3(k)][p];
-        return diag > 0.0 ? sor_update(old, (offsum + src) / diag, omega) : old;  // an isolated site keeps its value
+        return diag > 0.0 ? sor_update(old, diag, offsum, src, omega) : old;  // an isolated site keeps its value
     };
     fetch(zs - 2);
     commit(zs - 2);
@@ -798,53 +684,42 @@ template <typename T>
 void launch_sor(const Scalars& S, const Fields<T>& F, int color, double omega, bool split, hipStream_t st) {
     const unsigned n = S.ncolor == 3 ? S.ndomain : (unsigned)(S.nx / 2) * S.ny * (S.z1 - S.z0 + 1);
     if (split)
-        hipLaunchKernelGGL((k_sor<T, true>), dim3(site_blocks(n)), dim3(kBlock), 0, st, S, F, color, omega);
+        launch_sor_col<T>(S, F, color, omega, nullptr, st);
     else
-        hipLaunchKernelGGL((k_sor<T, false>), dim3(site_blocks(n)), dim3(kBlock), 0, st, S, F, color, omega);
+        hipLaunchKernelGGL(k_sor<T>, dim3(site_blocks(n)), dim3(kBlock), 0, st, S, F, color, omega);
 }
 
 // Residual r = s + A phi: FP64 partial sums of r.r, s.s and phi over the domain.
 // The operands are fetched for a lattice site whether or not i lies in the domain (outside
 // it: a wall layer, or the last site past the end) and the sums take zeros there, so the
 // loads of the sites a thread handles carry no branches and can overlap.
-template <typename T, bool SP = false>
+template <typename T>
 __device__ __forceinline__ void residual_body(const Scalars& S, const Fields<T>& F, unsigned i, double (&v)[3]) {
     const unsigned k = i < S.N ? i : S.N - 1;
     int x, y, z;
     site_xyz(k, S, x, y, z);
     const bool in = i < S.N && z >= S.z0 && z <= S.z1;
-    const double p = F.phi[cidx<SP>(S, k, (x + y + z) & 1)];
+    const double p = F.phi[k];
     double diag, offsum, src;
-    poisson_row<T, SP>(k, x, y, z, S, F, diag, offsum, src);
-    const double res = src + offsum - diag * p;
+    poisson_row<T>(k, x, y, z, S, F, diag, offsum, src);
+    const double res = row_residual(p, diag, offsum, src);
     v[0] = in ? res * res : 0.0;
     v[1] = in ? src * src : 0.0;
     v[2] = in ? p : 0.0;
 }
 
-// Each thread takes kResSites sites, kBlock apart (a workgroup covers kResSites x kBlock
-// consecutive sites), and sums them in order before the block reduction: fewer records
-// for the reducer to read.  From site-order fields (SP false) the kernel can also write
-// the colour-split copies of the potential and charge (phis, qs non-null) for the
-// multigrid solve that follows.
-template <typename T, bool SP>
-__global__ __launch_bounds__(kBlock) void k_residual(Scalars S, Fields<T> F, double* __restrict__ phis,
-                                                     T* __restrict__ qs) {
+// Lattices with an odd axis.  Each thread takes kResSites sites, kBlock apart (a workgroup covers
+// kResSites x kBlock consecutive sites), and sums them in order before the block reduction: fewer
+// records for the reducer to read.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_residual(Scalars S, Fields<T> F) {
     const unsigned nb = gridDim.x, b = blockIdx.x;
     const unsigned lb = (b & 7u) * (nb >> 3) + (b >> 3);  // XCD-contiguous ranges, as xcd_linear
     double acc[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < kResSites; ++j) {
-        const unsigned i = (lb * kResSites + j) * kBlock + threadIdx.x;
-        if (!SP && phis && i < S.N) {
-            int x, y, z;
-            site_xyz(i, S, x, y, z);
-            const unsigned o = cidx<true>(S, i, (x + y + z) & 1);
-            phis[o] = F.phi[i];
-            qs[o] = F.q[i];
-        }
         double v[3];
-        residual_body<T, SP>(S, F, i, v);
+        residual_body<T>(S, F, (lb * kResSites + j) * kBlock + threadIdx.x, v);
         acc[0] += v[0];
         acc[1] += v[1];
         acc[2] += v[2];
@@ -853,16 +728,16 @@ __global__ __launch_bounds__(kBlock) void k_residual(Scalars S, Fields<T> F, dou
     block_reduce_store<3>(acc, mx, F.red, blockIdx.x, gridDim.x);
 }
 
-unsigned residual_blocks(unsigned n) { return site_blocks((n + kResSites - 1) / kResSites); }
+unsigned residual_blocks(const Scalars& S) {
+    return columns_fit(S) ? residual_col_blocks(S) : site_blocks((S.N + kResSites - 1) / kResSites);
+}
 
 template <typename T>
-void launch_residual(const Scalars& S, const Fields<T>& F, unsigned nblk, bool split, double* phis, T* qs,
-                     hipStream_t st) {
-    if (split)
-        hipLaunchKernelGGL((k_residual<T, true>), dim3(nblk), dim3(kBlock), 0, st, S, F, (double*)nullptr,
-                           (T*)nullptr);
+void launch_residual(const Scalars& S, const Fields<T>& F, bool split, double* phis, T* qs, hipStream_t st) {
+    if (columns_fit(S))
+        launch_residual_col<T>(S, F, split, phis, qs, st);
     else
-        hipLaunchKernelGGL((k_residual<T, false>), dim3(nblk), dim3(kBlock), 0, st, S, F, phis, qs);
+        hipLaunchKernelGGL(k_residual<T>, dim3(residual_blocks(S)), dim3(kBlock), 0, st, S, F);
 }
 
 // Gauge mean(phi) = 0 over the domain (scal[3] = sum of phi), or phi = 0 when zero != 0.
@@ -941,10 +816,6 @@ void launch_phi_extrapolate(const Scalars& S, double* phi, double* prev, double*
 // eight children; the correction is interpolated trilinearly (weights 3/4, 1/4 per axis),
 // falling back to the parent across a zero face.  Smoothing is red-black Gauss-Seidel.
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ unsigned lid(const MGLevel& L, int x, int y, int z) {
-    return (unsigned)x + (unsigned)L.nx * ((unsigned)y + (unsigned)L.ny * (unsigned)z);
-}
-
 // Fine-level face coefficient between (x, y, z) and its +k neighbour: zero unless both
 // cells are in the Poisson domain.
 template <typename T>
@@ -1047,30 +918,12 @@ void launch_mg_smooth(const MGLevel& L, int color, double omega, hipStream_t st)
     hipLaunchKernelGGL(k_mg_smooth, dim3(site_blocks(n)), dim3(kBlock), 0, st, L, color, omega);
 }
 
-// Start of a coarse grid's correction: zero, except that with red_omega > 0 the red cells
-// ((I + J + K) even) take the first red pass of the pre-smoothing here.  From a zero
-// correction every neighbour term of that pass vanishes and it reduces to
-// omega s / diag, written as the sweep writes it (same operand order), so the grid's
-// first separate pass can be skipped.
-__device__ __forceinline__ void coarse_start(const MGLevel& C, int I, int J, int K, unsigned t, double s,
-                                             double red_omega) {
-    double v = 0.0;
-    if (red_omega > 0.0 && ((I + J + K) & 1) == 0) {
-        const int xm = wrapc(I - 1, C.nx), ym = wrapc(J - 1, C.ny), zm = wrapc(K - 1, C.nz);
-        const double diag = C.ax[t] + C.ax[lid(C, xm, J, K)] + C.ay[t] + C.ay[lid(C, I, ym, K)] + C.az[t] +
-                            C.az[lid(C, I, J, zm)];
-        if (diag > 0.0) {
-            const double p = 0.0, off = 0.0;
-            v = p + red_omega * ((off + s) / diag - p);
-        }
-    }
-    C.phi[t] = v;
-}
-
 // Residuals of the eight lattice cells under coarse cell t, summed.  The eight rows
 // share their stencil points: the 2x2x2 block and the four neighbours across each of its
 // six faces (32 sites), loaded once each.  Rows as in poisson_row, same operand order.
-template <typename T, bool SP = false>
+// The children are summed along x, then y, then z, as the column kernel sums
+// them.
+template <typename T>
 __device__ __forceinline__ void restrict_fine_body(const Scalars& S, const Fields<T>& F, const MGLevel& C, unsigned t,
                                                    double red_omega = 0.0) {
     if (t >= C.n) return;
@@ -1086,7 +939,6 @@ __device__ __forceinline__ void restrict_fine_body(const Scalars& S, const Field
     auto at = [&](int a, int b, int c) {
         return (unsigned)xs[a] + (unsigned)S.nx * ((unsigned)ys[b] + (unsigned)S.ny * (unsigned)zs[c]);
     };
-    auto col = [&](int a, int b, int c) { return (xs[a] + ys[b] + zs[c]) & 1; };
     double P[4][4][4];
     T E[4][4][4];  // permittivity in its storage precision (exactly widened where used)
 #pragma unroll
@@ -1098,71 +950,57 @@ __device__ __forceinline__ void restrict_fine_body(const Scalars& S, const Field
                 const int outer = (a == 0 || a == 3) + (b == 0 || b == 3) + (c == 0 || c == 3);
                 if (outer <= 1) {
                     const unsigned g = at(a, b, c);
-                    P[c][b][a] = F.phi[cidx<SP>(S, g, col(a, b, c))];
+                    P[c][b][a] = F.phi[g];
                     E[c][b][a] = F.eps[g];
                 }
             }
     const double mean = F.scal[0];
     double sum = 0.0;
 #pragma unroll
-    for (int c = 1; c < 3; ++c)
+    for (int c = 1; c < 3; ++c) {
+        double plane = 0.0;
 #pragma unroll
-        for (int b = 1; b < 3; ++b)
+        for (int b = 1; b < 3; ++b) {
+            double line = 0.0;
 #pragma unroll
             for (int a = 1; a < 3; ++a) {
                 const int z = zs[c];
                 if (z < S.z0 || z > S.z1) continue;
                 const double ei = (double)E[c][b][a];
-                double diag = 0.0, off = 0.0, pol = 0.0;
-                {
-                    const double ea = 0.5 * (ei + (double)E[c][b][a - 1]), eb = 0.5 * (ei + (double)E[c][b][a + 1]);
-                    diag += ea + eb;
-                    off += ea * P[c][b][a - 1] + eb * P[c][b][a + 1];
-                    pol += S.E_ext[0] * (eb - ea);
-                }
-                {
-                    const double ea = 0.5 * (ei + (double)E[c][b - 1][a]), eb = 0.5 * (ei + (double)E[c][b + 1][a]);
-                    diag += ea + eb;
-                    off += ea * P[c][b - 1][a] + eb * P[c][b + 1][a];
-                    pol += S.E_ext[1] * (eb - ea);
-                }
-                if (!(S.walls && z == S.z0)) {
-                    const double ea = 0.5 * (ei + (double)E[c - 1][b][a]);
-                    diag += ea;
-                    off += ea * P[c - 1][b][a];
-                    pol -= S.E_ext[2] * ea;
-                }
-                if (!(S.walls && z == S.z1)) {
-                    const double eb = 0.5 * (ei + (double)E[c + 1][b][a]);
-                    diag += eb;
-                    off += eb * P[c + 1][b][a];
-                    pol += S.E_ext[2] * eb;
-                }
-                double src = (double)F.q[cidx<SP>(S, at(a, b, c), col(a, b, c))];
+                const double xl = ei + (double)E[c][b][a - 1], xh = ei + (double)E[c][b][a + 1];
+                const double yl = ei + (double)E[c][b - 1][a], yh = ei + (double)E[c][b + 1][a];
+                const double zl = S.walls && z == S.z0 ? 0.0 : ei + (double)E[c - 1][b][a];
+                const double zh = S.walls && z == S.z1 ? 0.0 : ei + (double)E[c + 1][b][a];
+                double diag, off;
+                poisson_sums(xl, xh, yl, yh, zl, zh, P[c][b][a - 1], P[c][b][a + 1], P[c][b - 1][a], P[c][b + 1][a],
+                             P[c - 1][b][a], P[c + 1][b][a], diag, off);
+                double src = (double)F.q[at(a, b, c)];
                 if (S.walls && z == S.z0) src += S.sigma0;
                 if (S.walls && z == S.z1) src += S.sigma1;
-                if (S.polar) src -= pol;
+                if (S.polar) src -= poisson_polar(S, xl, xh, yl, yh, zl, zh);
                 src -= mean;
-                sum += src + off - diag * P[c][b][a];
+                line += row_residual(P[c][b][a], diag, off, src);
             }
+            plane += line;
+        }
+        sum += plane;
+    }
     C.s[t] = sum;
     coarse_start(C, I, J, K, t, sum, red_omega);
 }
 
-template <typename T, bool SP>
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_mg_restrict_fine(Scalars S, Fields<T> F, MGLevel C, double red_omega) {
-    restrict_fine_body<T, SP>(S, F, C, xcd_linear(), red_omega);
+    restrict_fine_body<T>(S, F, C, xcd_linear(), red_omega);
 }
 
 template <typename T>
 void launch_mg_restrict_fine(const Scalars& S, const Fields<T>& F, const MGLevel& c, bool split, double red_omega,
                              hipStream_t st) {
     if (split)
-        hipLaunchKernelGGL((k_mg_restrict_fine<T, true>), dim3(site_blocks(c.n)), dim3(kBlock), 0, st, S, F, c,
-                           red_omega);
+        launch_restrict_col<T>(S, F, c, red_omega, st);
     else
-        hipLaunchKernelGGL((k_mg_restrict_fine<T, false>), dim3(site_blocks(c.n)), dim3(kBlock), 0, st, S, F, c,
-                           red_omega);
+        hipLaunchKernelGGL(k_mg_restrict_fine<T>, dim3(site_blocks(c.n)), dim3(kBlock), 0, st, S, F, c, red_omega);
 }
 
 __device__ __forceinline__ void restrict_body(const MGLevel& Fl, const MGLevel& C, unsigned t, double red_omega = 0.0) {
@@ -1262,20 +1100,18 @@ __device__ __forceinline__ void prolong_fine_body(const Scalars& S, const Fields
 // Trilinear correction of one lattice site from the coarse potentials P of the cells
 // (I - 1 .. I + 1) x (J - 1 .. J + 1) x (K - 1 .. K + 1): xo, yo, zo index the site's own
 // coarse cell and its neighbour towards the site, weighted 3/4 and 1/4 (wzs carries the
-// fall-back to the parent across a wall).  The terms and their order are those of
-// prolong_fine_body.
+// fall-back to the parent across a wall).  Interpolated along z, then x, then y, as the
+// column kernel does it.
 __device__ __forceinline__ double prolong_corr(const double (&P)[3][3][3], const int (&xo)[2], const int (&yo)[2],
                                                const int (&zo)[2], const double (&wzs)[2]) {
-#pragma clang fp contract(off)
-    const double wxs[2] = {0.75, 0.25}, wys[2] = {0.75, 0.25};
-    double v = 0.0;
+    double row[2];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) v += wxs[a] * wys[b] * wzs[c] * P[zo[c]][yo[b]][xo[a]];
-    return v;
+    for (int b = 0; b < 2; ++b) {
+        const double own = prolong_z(wzs[0], P[zo[0]][yo[b]][xo[0]], wzs[1], P[zo[1]][yo[b]][xo[0]]);
+        const double nbr = prolong_z(wzs[0], P[zo[0]][yo[b]][xo[1]], wzs[1], P[zo[1]][yo[b]][xo[1]]);
+        row[b] = prolong_q(own, nbr);
+    }
+    return prolong_q(row[0], row[1]);
 }
 
 __device__ __forceinline__ void load_coarse27(const MGLevel& C, int I, int J, int K, double (&P)[3][3][3]) {
@@ -1289,8 +1125,7 @@ __device__ __forceinline__ void load_coarse27(const MGLevel& C, int I, int J, in
 }
 
 // The same, one thread per coarse cell for its eight lattice children: the 3x3x3 coarse
-// neighbourhood is loaded once into registers and each child is interpolated with exactly
-// the expression and order of prolong_fine_body (bit-identical); the two x-children of a
+// neighbourhood is loaded once into registers; the two x-children of a
 // row are read and written as one 16-byte pair (colour-split, SP: one value in each
 // colour half).
 template <typename T, bool SP>
@@ -1354,72 +1189,6 @@ void launch_mg_prolong_fine(const Scalars& S, const Fields<T>& F, const MGLevel&
     else
         hipLaunchKernelGGL((k_mg_prolong_fine<T, false>), dim3(site_blocks(c.n)), dim3(kBlock), 0, st, S, F, c);
 }
-
-// The interpolation onto the lattice fused with the first red pass of the post-smoothing
-// (colour-split fields).  One thread per coarse cell.  Its four red children take the
-// interpolated correction and then their Gauss-Seidel update; their six black neighbours
-// (three in the block, three around it) are interpolated on the fly from the same 3x3x3
-// coarse registers.  Its four black children's interpolated values go to blk (indexed
-// like the black half), and the black pass that follows reads them from there: written in
-// place they could reach a neighbouring thread that still needs the old values.  Every
-// value is the one the separate interpolation and red pass compute: the same expressions
-// in the same order.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_mg_prolong_red_fine(Scalars S, Fields<T> F, MGLevel C, double omega,
-                                                                double* __restrict__ blk) {
-    const unsigned t = xcd_linear();
-    if (t >= C.n) return;
-    int I, J, K;
-    level_xyz(t, C, I, J, K);
-    double P[3][3][3];
-    load_coarse27(C, I, J, K, P);
-    // correction at the lattice site (2I + rx, 2J + ry, 2K + rz), rx, ry, rz in -1..2 (its
-    // coarse cell and the neighbour towards it lie in P); the offsets are compile-time
-    // constants once the loops below unroll, so P stays in registers
-    auto corr_at = [&](int rx, int ry, int rz) {
-        const int dx = (rx & 1) ? 1 : -1, dy = (ry & 1) ? 1 : -1, dz = (rz & 1) ? 1 : -1;
-        const int xo[2] = {1 + (rx >> 1), 1 + (rx >> 1) + dx}, yo[2] = {1 + (ry >> 1), 1 + (ry >> 1) + dy},
-                  zo[2] = {1 + (rz >> 1), 1 + (rz >> 1) + dz};  // >> 1: floor, also for -1
-        const int Kw = wrapc(K + (rz >> 1), C.nz);
-        const bool zwrap = S.walls && (Kw + dz < 0 || Kw + dz >= C.nz);
-        const double wz = zwrap ? 0.0 : 0.25;
-        const double wzs[2] = {1.0 - wz, wz};
-        return prolong_corr(P, xo, yo, zo, wzs);
-    };
-#pragma unroll
-    for (int cz = 0; cz < 2; ++cz)
-#pragma unroll
-        for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-            for (int cx = 0; cx < 2; ++cx) {
-                const int x = 2 * I + cx, y = 2 * J + cy, z = 2 * K + cz;
-                if (z < S.z0 || z > S.z1) continue;
-                const unsigned i = (unsigned)x + (unsigned)S.nx * ((unsigned)y + (unsigned)S.ny * (unsigned)z);
-                const int col = (cx + cy + cz) & 1;
-                const double p = F.phi[cidx<true>(S, i, col)] + corr_at(cx, cy, cz);
-                if (col) {
-                    blk[i >> 1] = p;
-                    continue;
-                }
-                double diag, offsum, src;
-                poisson_row_v<T, true>(
-                    i, x, y, z, S, F,
-                    [&](unsigned j, int c, int ox, int oy, int oz) {
-                        return F.phi[cidx<true>(S, j, c)] + corr_at(cx + ox, cy + oy, cz + oz);
-                    },
-                    diag, offsum, src);
-                double v = p;
-                if (diag > 0.0) v = sor_update(p, (offsum + src) / diag, omega);
-                F.phi[cidx<true>(S, i, 0)] = v;
-            }
-}
-
-template <typename T>
-void launch_mg_prolong_red_fine(const Scalars& S, const Fields<T>& F, const MGLevel& c, double omega, double* blk,
-                                hipStream_t st) {
-    hipLaunchKernelGGL(k_mg_prolong_red_fine<T>, dim3(site_blocks(c.n)), dim3(kBlock), 0, st, S, F, c, omega, blk);
-}
-
 
 __device__ __forceinline__ void prolong_body(const MGLevel& C, const MGLevel& Fl, unsigned i) {
     if (i >= Fl.n) return;
@@ -2581,7 +2350,7 @@ template <typename T> void launch_field_e(const Scalars& S, const Fields<T>& F, 
     template void launch_moments<T>(const Scalars&, const Fields<T>&, unsigned, hipStream_t);                  \
     template void launch_virtual<T>(const Scalars&, const Fields<T>&, hipStream_t);                            \
     template void launch_sor<T>(const Scalars&, const Fields<T>&, int, double, bool, hipStream_t);             \
-    template void launch_residual<T>(const Scalars&, const Fields<T>&, unsigned, bool, double*, T*, hipStream_t); \
+    template void launch_residual<T>(const Scalars&, const Fields<T>&, bool, double*, T*, hipStream_t);       \
     template void launch_phi_finalize<T>(const Scalars&, const Fields<T>&, int, const double*, hipStream_t);   \
     template void launch_force<T>(const Scalars&, const Fields<T>&, hipStream_t);                              \
     template void launch_fused<T>(const Scalars&, const Fields<T>&, hipStream_t);                              \
@@ -2602,9 +2371,6 @@ template <typename T> void launch_field_e(const Scalars& S, const Fields<T>& F, 
     template void launch_mg_restrict_fine<T>(const Scalars&, const Fields<T>&, const MGLevel&, bool, double,      \
                                              hipStream_t);                                                       \
     template void launch_mg_prolong_fine<T>(const Scalars&, const Fields<T>&, const MGLevel&, bool, hipStream_t); \
-    template void launch_mg_prolong_red_fine<T>(const Scalars&, const Fields<T>&, const MGLevel&, double, double*, \
-                                                hipStream_t);                                                      \
-    template void launch_sor_black_from<T>(const Scalars&, const Fields<T>&, double, const double*, hipStream_t); \
     template void launch_sor_rb<T>(const Scalars&, const Fields<T>&, const double*, double*, double, hipStream_t);
 
 EK_INST(float)
