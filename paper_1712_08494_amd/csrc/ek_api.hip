@@ -109,8 +109,8 @@ struct ek_ctx {
     int32_t* rp_origin = nullptr;
     int32_t *rp_nb = nullptr, *rp_nnb = nullptr;  // particles whose projection boxes meet
     int16_t* rp_cnt = nullptr;
-    uint8_t *rp_inside = nullptr, *rp_event = nullptr;
-    double *rp_evm = nullptr, *rp_ptot = nullptr;
+    uint8_t* rp_inside = nullptr;
+    double *rp_part = nullptr, *rp_ptot = nullptr;
     void* rp_share = nullptr;
     std::vector<double> px0, hrad;
     // scratch
@@ -1093,19 +1093,15 @@ static ek_status step_rest(ek_ctx* c) {
         launch_particle_step<T>(c->S, F, c->np, c->plink_off, c->plink_idx, c->psite_off, c->psite_idx,
                                 c->px[c->pcur], c->pv[c->pcur], c->prad, c->pF, c->px[c->pcur ^ 1],
                                 c->pv[c->pcur ^ 1], c->p.particle_rho, c->p.k_hertz, c->p.eta, c->p.move_particles,
-                                c->st);
+                                c->rp_part, c->st);
         c->pcur ^= 1;
     }
     if (c->S.reproject) {
         Timer tm(c, EK_T_PARTICLE);
         EK_KT(EK_K_REPROJECT);
-        const size_t N = c->N;
-        EK_HIP(hipMemcpyAsync(c->flags_old, c->flags, N, hipMemcpyDeviceToDevice, c->st));
-        EK_HIP(hipMemcpyAsync(c->owner_old, c->owner, N * 4, hipMemcpyDeviceToDevice, c->st));
-        EK_HIP(hipMemcpyAsync(c->psif_old, c->psif, N * c->esz, hipMemcpyDeviceToDevice, c->st));
         Reproj<T> P{c->np, c->px[c->pcur], c->pv[c->pcur], c->prad, c->pQ, c->p.particle_rho, c->flags, c->owner,
-                    (T*)c->psif, (T*)c->qc, c->flags_old, c->owner_old, (const T*)c->psif_old, c->rp_origin,
-                    c->rp_cnt, c->rp_inside, c->rp_event, c->rp_evm, (T*)c->rp_share, c->rp_ptot, c->rp_nb, c->rp_nnb,
+                    (T*)c->psif, (T*)c->qc, c->flags_old, c->owner_old, (T*)c->psif_old, c->rp_origin,
+                    c->rp_cnt, c->rp_inside, c->rp_part, (T*)c->rp_share, c->rp_ptot, c->rp_nb, c->rp_nnb,
                     c->plist, c->npl_dev};
         launch_reproject<T>(c->S, F, P, c->st);
     }
@@ -1336,8 +1332,7 @@ static ek_status allocate_all(ek_ctx* c, const HostGeom& g, int np) {
             EK_TRY(dalloc(c, (void**)&c->rp_nnb, np * 4));
             EK_TRY(dalloc(c, (void**)&c->rp_cnt, np * B3 * 2));
             EK_TRY(dalloc(c, (void**)&c->rp_inside, np * B3));
-            EK_TRY(dalloc(c, (void**)&c->rp_event, np * B3));
-            EK_TRY(dalloc(c, (void**)&c->rp_evm, 3 * np * B3 * 8));
+            EK_TRY(dalloc(c, (void**)&c->rp_part, 4 * np * box_groups(c->S, (int)np) * 8));
             EK_TRY(dalloc(c, &c->rp_share, (size_t)2 * N * es));
             EK_TRY(dalloc(c, (void**)&c->rp_ptot, np * 8));
         }

@@ -226,12 +226,13 @@ void launch_lag_scale(double* spec, const double* tab, int nx, int ny, int nz, h
 // populations of component c at time t of a moment-state context (FP64, 19 N, f not g)
 template <typename T> void launch_export_pop(const Scalars& S, const Fields<T>& F, int c, double* out, hipStream_t st);
 // one workgroup per particle: link momenta, q_c E over its sites, Hertz and lubrication
-// against every other particle, then symplectic Euler into xn, vn (pF receives the force)
+// against every other particle, then symplectic Euler into xn, vn (pF receives the force).
+// Moving particles: part holds 3 doubles per workgroup of their boxes
 template <typename T>
 void launch_particle_step(const Scalars& S, const Fields<T>& F, int np, const int32_t* link_off,
                           const int32_t* link_idx, const int32_t* site_off, const int32_t* site_idx, const double* x,
                           const double* v, const double* r, double* pF, double* xn, double* vn, double rho_p,
-                          double k_h, double eta, int move, hipStream_t st);
+                          double k_h, double eta, int move, double* part, hipStream_t st);
 template <typename T> void launch_observe(const Scalars& S, const Fields<T>& F, unsigned nblk, hipStream_t st);
 
 // Projection of moving particles after their step (ek_params.reproject).  Work arrays: the
@@ -251,14 +252,13 @@ struct Reproj {
     int32_t* owner;
     T* psif;
     T* qc;
-    const uint8_t* flags_old;  // copies taken before the projection
-    const int32_t* owner_old;
-    const T* psif_old;
+    uint8_t* flags_old;  // the geometry before the projection, of box sites
+    int32_t* owner_old;
+    T* psif_old;
     int32_t* origin;     // 3 np: lowest lattice corner of each particle's box (not wrapped)
     int16_t* cnt;        // np x box^3: sub-cells of the site inside the particle
     uint8_t* inside;     // np x box^3: the site's centre strictly inside the particle
-    uint8_t* event;      // np x box^3: 1 covered, 2 uncovered (for the particle handling it)
-    double* evm;         // 3 x np x box^3: the particle's momentum change from that site
+    double* part;        // 4 per workgroup of a box: momentum change, solid fraction
     T* share;            // 2 N: ion shares (mean density, charge) of a site losing its fluid
     double* ptot;        // np: summed solid fraction of each particle's sites
     int32_t* nb;         // np x np: per particle, the particles whose boxes meet its box, ascending (itself included)
@@ -266,6 +266,7 @@ struct Reproj {
     int32_t* plist;      // the context's particle-path list, rebuilt from the boxes
     int32_t* npl;        // its length (device)
 };
+unsigned box_groups(const Scalars& S, int np);  // workgroups that walk a particle's box
 template <typename T>
 void launch_reproject(const Scalars& S, const Fields<T>& F, const Reproj<T>& P, hipStream_t st);
 // the observables from a fixed grid of nblk workgroups (grid-stride), partial sums in red

@@ -1995,6 +1995,59 @@ template <typename T> void launch_fused(const Scalars& S, const Fields<T>& F, hi
 // order; then symplectic Euler (v, then x).  All read the positions and velocities of the
 // step's start and write the next buffers, so the particles are independent.
 // ------------------------------------------------------------------------------------
+// Moving particles: the link momenta and q_c E over a particle's box, three sums per workgroup of the
+// box (box_groups of them; one workgroup a particle left most of the chip idle:
+// 25 spheres at 128^3 164 us, now 22 here and 5 in k_particle_step).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_particle_box(Scalars S, Fields<T> F, const double* __restrict__ x,
+                                                         const double* __restrict__ v, double* __restrict__ part) {
+    const int a = blockIdx.x;
+    double f[3] = {0.0, 0.0, 0.0};
+    // No link or site lists (the mask moves): the particle's box around its position at
+    // the step's start.  Each link from a fluid site i to a site of this particle
+    // returned f*_d - corr into i's opposite direction, so f*_d is recovered from it.
+    const int B = S.rp_box, B3 = B * B * B;
+    const int ox = (int)floor(x[3 * a]) - S.rp_half, oy = (int)floor(x[3 * a + 1]) - S.rp_half,
+              oz = (int)floor(x[3 * a + 2]) - S.rp_half;
+    const size_t N = S.N;
+    for (int t = blockIdx.y * kBlock + threadIdx.x; t < B3; t += kBlock * gridDim.y) {
+        const int sx = wrapc(ox + t % B, S.nx), sy = wrapc(oy + (t / B) % B, S.ny), sz = wrapc(oz + t / (B * B), S.nz);
+        const unsigned i = (unsigned)sx + (unsigned)S.nx * ((unsigned)sy + (unsigned)S.ny * (unsigned)sz);
+        if (F.owner[i] == a) {
+            const double qv = (double)F.qc[i];
+            f[0] += qv * efield(0, sx, sy, sz, F.phi, S);
+            f[1] += qv * efield(1, sx, sy, sz, F.phi, S);
+            f[2] += qv * efield(2, sx, sy, sz, F.phi, S);
+        }
+        if (F.flags[i] & 1u) continue;
+        const Nbr o = make_nbr(sx, sy, sz, S);
+        for (int d = 0; d < kQ; ++d) {
+            if (d == kRest) continue;
+            const unsigned j = i + offset_of(o, d);
+            if (!(F.flags[j] & 1u) || F.owner[j] != a) continue;
+            const T cv = T(vx(d)) * T(v[3 * a]) + T(vy(d)) * T(v[3 * a + 1]) + T(vz(d)) * T(v[3 * a + 2]);
+            for (int c = 0; c < 2; ++c) {
+                const T rs = T(S.rref[c]) + F.mom[(size_t)c * N + i];
+                const T corr = T(6) * T(weight(d)) * rs * cv;
+                const double gs = (double)F.fn[c][(size_t)opposite(d) * N + i] + (double)corr;
+                const double dp = 2.0 * (gs + weight(d) * S.rref[c]) - (double)corr;
+                f[0] += dp * vx(d);
+                f[1] += dp * vy(d);
+                f[2] += dp * vz(d);
+            }
+        }
+    }
+    __shared__ double sm[3][kBlock];
+    for (int k = 0; k < 3; ++k) sm[k][threadIdx.x] = f[k];
+    __syncthreads();
+    for (int h = kBlock / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h)
+            for (int k = 0; k < 3; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x < 3) part[((size_t)a * gridDim.y + blockIdx.y) * 3 + threadIdx.x] = sm[threadIdx.x][0];
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_particle_step(Scalars S, Fields<T> F, int np, const int32_t* link_off,
                                                           const int32_t* link_idx, const int32_t* site_off,
@@ -2002,44 +2055,12 @@ __global__ __launch_bounds__(kBlock) void k_particle_step(Scalars S, Fields<T> F
                                                           const double* __restrict__ v, const double* __restrict__ rad,
                                                           double* __restrict__ pF, double* __restrict__ xn,
                                                           double* __restrict__ vn, double rho_p, double k_h, double eta,
-                                                          int move) {
+                                                          int move, const double* __restrict__ part, int groups) {
     const int a = blockIdx.x;
     double f[3] = {0.0, 0.0, 0.0};
-    if (S.reproject) {
-        // No link or site lists (the mask moves): the particle's box around its position at
-        // the step's start.  Each link from a fluid site i to a site of this particle
-        // returned f*_d - corr into i's opposite direction, so f*_d is recovered from it.
-        const int B = S.rp_box, B3 = B * B * B;
-        const int ox = (int)floor(x[3 * a]) - S.rp_half, oy = (int)floor(x[3 * a + 1]) - S.rp_half,
-                  oz = (int)floor(x[3 * a + 2]) - S.rp_half;
-        const size_t N = S.N;
-        for (int t = threadIdx.x; t < B3; t += blockDim.x) {
-            const int sx = wrapc(ox + t % B, S.nx), sy = wrapc(oy + (t / B) % B, S.ny), sz = wrapc(oz + t / (B * B), S.nz);
-            const unsigned i = (unsigned)sx + (unsigned)S.nx * ((unsigned)sy + (unsigned)S.ny * (unsigned)sz);
-            if (F.owner[i] == a) {
-                const double qv = (double)F.qc[i];
-                f[0] += qv * efield(0, sx, sy, sz, F.phi, S);
-                f[1] += qv * efield(1, sx, sy, sz, F.phi, S);
-                f[2] += qv * efield(2, sx, sy, sz, F.phi, S);
-            }
-            if (F.flags[i] & 1u) continue;
-            const Nbr o = make_nbr(sx, sy, sz, S);
-            for (int d = 0; d < kQ; ++d) {
-                if (d == kRest) continue;
-                const unsigned j = i + offset_of(o, d);
-                if (!(F.flags[j] & 1u) || F.owner[j] != a) continue;
-                const T cv = T(vx(d)) * T(v[3 * a]) + T(vy(d)) * T(v[3 * a + 1]) + T(vz(d)) * T(v[3 * a + 2]);
-                for (int c = 0; c < 2; ++c) {
-                    const T rs = T(S.rref[c]) + F.mom[(size_t)c * N + i];
-                    const T corr = T(6) * T(weight(d)) * rs * cv;
-                    const double gs = (double)F.fn[c][(size_t)opposite(d) * N + i] + (double)corr;
-                    const double dp = 2.0 * (gs + weight(d) * S.rref[c]) - (double)corr;
-                    f[0] += dp * vx(d);
-                    f[1] += dp * vy(d);
-                    f[2] += dp * vz(d);
-                }
-            }
-        }
+    if (S.reproject) {  // summed by k_particle_box
+        for (int t = threadIdx.x; t < groups; t += blockDim.x)
+            for (int k = 0; k < 3; ++k) f[k] += part[((size_t)a * groups + t) * 3 + k];
     } else {
         for (int t = link_off[a] + threadIdx.x; t < link_off[a + 1]; t += blockDim.x) {
             const double* rec = F.linkdp + (size_t)link_idx[t] * 6;
@@ -2106,10 +2127,15 @@ template <typename T>
 void launch_particle_step(const Scalars& S, const Fields<T>& F, int np, const int32_t* link_off,
                           const int32_t* link_idx, const int32_t* site_off, const int32_t* site_idx, const double* x,
                           const double* v, const double* r, double* pF, double* xn, double* vn, double rho_p,
-                          double k_h, double eta, int move, hipStream_t st) {
+                          double k_h, double eta, int move, double* part, hipStream_t st) {
     if (np <= 0) return;
+    int groups = 0;
+    if (S.reproject) {
+        groups = (int)box_groups(S, np);
+        hipLaunchKernelGGL(k_particle_box<T>, dim3(np, groups), dim3(kBlock), 0, st, S, F, x, v, part);
+    }
     hipLaunchKernelGGL(k_particle_step<T>, dim3(np), dim3(kBlock), 0, st, S, F, np, link_off, link_idx, site_off,
-                       site_idx, x, v, r, pF, xn, vn, rho_p, k_h, eta, move);
+                       site_idx, x, v, r, pF, xn, vn, rho_p, k_h, eta, move, part, groups);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2357,7 +2383,7 @@ template <typename T> void launch_field_e(const Scalars& S, const Fields<T>& F, 
     template void launch_export_pop<T>(const Scalars&, const Fields<T>&, int, double*, hipStream_t);           \
     template void launch_particle_step<T>(const Scalars&, const Fields<T>&, int, const int32_t*, const int32_t*,  \
                                           const int32_t*, const int32_t*, const double*, const double*, const double*, \
-                                          double*, double*, double*, double, double, double, int, hipStream_t);                \
+                                          double*, double*, double*, double, double, double, int, double*, hipStream_t);       \
     template void launch_observe<T>(const Scalars&, const Fields<T>&, unsigned, hipStream_t);                  \
     template void launch_add_lo<T>(const T*, double*, unsigned, hipStream_t);                  \
     template void launch_observe_strided<T>(const Scalars&, const Fields<T>&, unsigned, double*, hipStream_t);                  \

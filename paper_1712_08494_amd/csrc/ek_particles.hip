@@ -14,20 +14,26 @@
 //
 // Layout.  Every particle owns a box of rp_box^3 sites centred on its new position, wide
 // enough to hold every site whose geometry the step can change (the move is below one site
-// per step) and their neighbours.  A few workgroups per particle walk its box, one thread
+// per step) and their neighbours.  box_groups workgroups per particle walk its box, one thread
 // per box site; sites in several boxes are resolved from all boxes that meet (the owner is
 // the lowest particle index with a covered sub-cell, a site is solid if its centre is
 // inside any particle), so every thread writes the same values there.  Each conversion is
 // handled by exactly one thread (of the new owner's box for a covered site, of the old
 // owner's for an uncovered one), and per-site work that adds (ion shares, charge) by the
-// lowest-indexed particle whose box holds the site.  Per-particle sums run in one
-// workgroup per particle in a fixed tree order, so results are deterministic.
+// lowest-indexed particle whose box holds the site.  Per-particle sums are taken per
+// workgroup in a fixed tree order and added in the order of the workgroups, so results are
+// deterministic.
+//
+// Bound by latency: a box has a few thousand sites.  With 25 spheres at 128^3 in FP32 the step's
+// projection takes 125 us (291 with at most eight workgroups a box, one for the sums, and copies
+// of the whole geometry), most of it the sub-cell counts (46) and the uncovered sites (37).
 #include "ek_device.h"
 
 namespace ek {
 
 namespace {
 
+constexpr int kSubsMost = 31;         // sub-cells per axis with moving particles (checked by the host)
 constexpr double kHalfDiag = 0.8661;  // above sqrt(3)/2: no sub-cell centre is further from its site
 
 struct BoxSite {
@@ -93,7 +99,8 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double (*s)[kBlock]) 
 }  // namespace
 
 // Pass 1: each particle's box origin, and for every box site the sub-cell count and the
-// centre test at the new position (the same arithmetic as the set-up projection).
+// centre test at the new position (the same arithmetic as the set-up projection), and a copy of
+// the geometry before the move (only box sites are looked up in it).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_rp_mark(Scalars S, Reproj<T> P) {
 #pragma clang fp contract(off)
@@ -104,6 +111,10 @@ __global__ __launch_bounds__(kBlock) void k_rp_mark(Scalars S, Reproj<T> P) {
     if (blockIdx.y == 0 && threadIdx.x == 0)
         for (int k = 0; k < 3; ++k) P.origin[3 * a + k] = org[k];
     const int B3 = S.rp_box * S.rp_box * S.rp_box, h = S.subs;
+    // sub-cell centres from their site, once per workgroup (a division each)
+    __shared__ double cell[kSubsMost];
+    for (int k = threadIdx.x; k < min(h, kSubsMost); k += kBlock) cell[k] = (k + 0.5) / h - 0.5;
+    __syncthreads();
     for (int t = blockIdx.y * kBlock + threadIdx.x; t < B3; t += kBlock * gridDim.y) {
         const BoxSite s = box_site(S, org, 0, t);
         const double dx = min_image((double)s.x - X, S.nx), dy = min_image((double)s.y - Y, S.ny),
@@ -115,12 +126,13 @@ __global__ __launch_bounds__(kBlock) void k_rp_mark(Scalars S, Reproj<T> P) {
             c = h * h * h;
         } else if (d - kHalfDiag <= R) {
             for (int ia = 0; ia < h; ++ia) {
-                const double sx = dx + ((ia + 0.5) / h - 0.5);
+                const double sx = dx + cell[ia];
                 for (int ib = 0; ib < h; ++ib) {
-                    const double sy = dy + ((ib + 0.5) / h - 0.5);
+                    const double sy = dy + cell[ib];
                     const double sxy = sx * sx + sy * sy;
+#pragma unroll 4
                     for (int ie = 0; ie < h; ++ie) {
-                        const double sz = dz + ((ie + 0.5) / h - 0.5);
+                        const double sz = dz + cell[ie];
                         if (sxy + sz * sz <= R * R) ++c;
                     }
                 }
@@ -129,20 +141,28 @@ __global__ __launch_bounds__(kBlock) void k_rp_mark(Scalars S, Reproj<T> P) {
         const size_t k = (size_t)a * B3 + t;
         P.cnt[k] = (int16_t)c;
         P.inside[k] = d2 < R * R;
+        // the geometry before the move: a site in several boxes is saved alike from each
+        P.flags_old[s.i] = P.flags[s.i];
+        P.owner_old[s.i] = P.owner[s.i];
+        P.psif_old[s.i] = P.psif[s.i];
     }
 }
 
 // Pass 1b: for each particle, the particles whose boxes meet its own, in ascending order.
 // Only they can hold a site of its box, so the later passes scan them instead of every box.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_rp_pairs(Scalars S, Reproj<T> P) {
-    const int a = blockIdx.x;
-    if (threadIdx.x != 0) return;
-    if (a == 0) *P.npl = 0;  // the particle-path list is rebuilt by k_rp_list
+__global__ __launch_bounds__(64) void k_rp_pairs(Scalars S, Reproj<T> P) {
+    const int a = blockIdx.x, lane = threadIdx.x;
+    if (a == 0 && lane == 0) *P.npl = 0;  // the particle-path list is rebuilt by k_rp_finish
     int m = 0;
-    for (int j = 0; j < P.np; ++j)
-        if (boxes_meet(S, P.origin, a, j)) P.nb[(size_t)a * P.np + m++] = j;
-    P.nnb[a] = m;
+    for (int j0 = 0; j0 < P.np; j0 += 64) {
+        const int j = j0 + lane;
+        const bool meet = j < P.np && boxes_meet(S, P.origin, a, j);
+        const unsigned long long all = __ballot(meet);
+        if (meet) P.nb[(size_t)a * P.np + m + __popcll(all & ((1ull << lane) - 1))] = j;
+        m += __popcll(all);
+    }
+    if (lane == 0) P.nnb[a] = m;
 }
 
 // Pass 2: the new solid mark, owner and fluid fraction of every box site, from all boxes.
@@ -175,20 +195,20 @@ __global__ __launch_bounds__(kBlock) void k_rp_resolve(Scalars S, Reproj<T> P) {
     }
 }
 
-// Pass 3: the conversions (momentum records, fresh fluid) and the ion shares.
+// Pass 3: the conversions (fresh fluid), the ion shares, and per workgroup the impulse of its
+// conversions and the solid fraction of its sites (four sums at P.part).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_rp_convert(Scalars S, Fields<T> F, Reproj<T> P) {
 #pragma clang fp contract(off)
     const int a = blockIdx.x;
     const int B3 = S.rp_box * S.rp_box * S.rp_box;
     const size_t N = S.N;
+    double sums[4] = {0.0, 0.0, 0.0, 0.0};
     for (int t = blockIdx.y * kBlock + threadIdx.x; t < B3; t += kBlock * gridDim.y) {
         const BoxSite s = box_site(S, P.origin, a, t);
-        const size_t k = (size_t)a * B3 + t;
-        P.event[k] = 0;
-        P.evm[3 * k] = P.evm[3 * k + 1] = P.evm[3 * k + 2] = 0.0;
-        if (wall_layer(S, s.z)) continue;
         const unsigned i = s.i;
+        if (P.owner[i] == a) sums[3] += 1.0 - (double)P.psif[i];
+        if (wall_layer(S, s.z)) continue;
         const bool was = P.flags_old[i] & 1, now = P.flags[i] & 1;
         const Nbr o = make_nbr(s.x, s.y, s.z, S);
         if (!was && now && P.owner[i] == a) {  // covered: its fluid momentum goes to the particle
@@ -201,8 +221,7 @@ __global__ __launch_bounds__(kBlock) void k_rp_convert(Scalars S, Fields<T> F, R
                     m[1] += g * vy(d);
                     m[2] += g * vz(d);
                 }
-            P.event[k] = 1;
-            for (int q = 0; q < 3; ++q) P.evm[3 * k + q] = m[q];
+            for (int q = 0; q < 3; ++q) sums[q] += m[q];
         }
         if (was && !now && P.owner_old[i] == a) {  // uncovered: fresh fluid moving with the particle
             const double v0 = P.v[3 * a], v1 = P.v[3 * a + 1], v2 = P.v[3 * a + 2];
@@ -234,8 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_rp_convert(Scalars S, Fields<T> F, R
                 dm[1] -= rb * v1;
                 dm[2] -= rb * v2;
             }
-            P.event[k] = 2;
-            for (int q = 0; q < 3; ++q) P.evm[3 * k + q] = dm[q];
+            for (int q = 0; q < 3; ++q) sums[q] += dm[q];
         }
         if (P.psif_old[i] > T(0) && P.psif[i] == T(0) && P.owner[i] == a) {  // its ions move away
             int cnt = 0;
@@ -251,6 +269,9 @@ __global__ __launch_bounds__(kBlock) void k_rp_convert(Scalars S, Fields<T> F, R
             }
         }
     }
+    __shared__ double sm[4][kBlock];
+    block_sum<4>(sums, sm);
+    if (threadIdx.x < 4) P.part[((size_t)a * gridDim.y + blockIdx.y) * 4 + threadIdx.x] = sm[threadIdx.x][0];
 }
 
 // Pass 4: the ion shares, gathered by each receiving site; the giving sites are emptied.
@@ -265,7 +286,7 @@ __global__ __launch_bounds__(kBlock) void k_rp_ions(Scalars S, Fields<T> F, Repr
         const unsigned i = s.i;
         const Nbr o = make_nbr(s.x, s.y, s.z, S);
         auto gives = [&](unsigned j, int zj) {
-            if (wall_layer(S, zj) || !(P.psif_old[j] > T(0) && P.psif[j] == T(0))) return false;
+            if (wall_layer(S, zj) || !(P.psif[j] == T(0) && P.psif_old[j] > T(0))) return false;
             // a site with no axis neighbour keeping fluid keeps its ions (no shares written)
             const int jx = (int)(j % (unsigned)S.nx), jy = (int)((j / (unsigned)S.nx) % (unsigned)S.ny);
             const Nbr oj = make_nbr(jx, jy, zj, S);
@@ -306,86 +327,79 @@ __global__ __launch_bounds__(kBlock) void k_rp_ions(Scalars S, Fields<T> F, Repr
 
 // Pass 5: per particle, the impulse of its conversions and the summed solid fraction.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_rp_sum(Scalars S, Reproj<T> P) {
-    const int a = blockIdx.x;
-    const int B3 = S.rp_box * S.rp_box * S.rp_box;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int t = threadIdx.x; t < B3; t += blockDim.x) {
-        const size_t k = (size_t)a * B3 + t;
-        if (P.event[k]) {
-            acc[0] += P.evm[3 * k];
-            acc[1] += P.evm[3 * k + 1];
-            acc[2] += P.evm[3 * k + 2];
-        }
-        const BoxSite s = box_site(S, P.origin, a, t);
-        if (P.owner[s.i] == a) acc[3] += 1.0 - (double)P.psif[s.i];
-    }
-    __shared__ double sm[4][kBlock];
-    block_sum<4>(acc, sm);
-    if (threadIdx.x == 0) {
-        const double R = P.rad[a];
-        const double m = P.rho_p * (4.0 / 3.0) * M_PI * R * R * R;
-        for (int q = 0; q < 3; ++q) P.v[3 * a + q] += sm[q][0] / m;
-        P.ptot[a] = sm[3][0];
-    }
+__global__ __launch_bounds__(64) void k_rp_sum(Scalars S, Reproj<T> P, int groups) {
+    const int a = blockIdx.x, k = threadIdx.x;
+    if (k >= 4) return;
+    double acc = 0.0;
+    for (int g = 0; g < groups; ++g) acc += P.part[((size_t)a * groups + g) * 4 + k];
+    const double R = P.rad[a];
+    const double m = P.rho_p * (4.0 / 3.0) * M_PI * R * R * R;
+    if (k < 3)
+        P.v[3 * a + k] += acc / m;
+    else
+        P.ptot[a] = acc;
 }
 
-// Pass 6: charge per site and the neighbour flag bits of every box site.
+// Pass 6: charge per site and the neighbour flag bits of every box site, and the particle-path
+// sites (flag bits 0, 1 or 3) into the context's list, in no particular order: every such site lies
+// in a box (a box reaches four sites beyond its sphere), and the list kernels handle each
+// listed site by itself.  One atomic per wave takes the places of its sites.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_rp_finish(Scalars S, Reproj<T> P) {
     const int a = blockIdx.x;
     const int B3 = S.rp_box * S.rp_box * S.rp_box;
     for (int t = blockIdx.y * kBlock + threadIdx.x; t < B3; t += kBlock * gridDim.y) {
         const BoxSite s = box_site(S, P.origin, a, t);
-        if (first_box(S, P, a, s.x, s.y, s.z) != a) continue;
         const unsigned i = s.i;
-        const int own = P.owner[i];
-        const double psis = 1.0 - (double)P.psif[i];
-        P.qc[i] = (own >= 0 && P.ptot[own] > 0.0) ? (T)(P.Q[own] * psis / P.ptot[own]) : T(0);
-        const Nbr o = make_nbr(s.x, s.y, s.z, S);
-        const uint8_t si = P.flags[i] & 1;
-        bool other = false;
-        for (int d = 0; d < kQ; ++d) {
-            if (d == kRest) continue;
-            if ((P.flags[i + offset_of(o, d)] & 1) != si) other = true;
+        bool listed = false;
+        if (first_box(S, P, a, s.x, s.y, s.z) == a) {
+            const int own = P.owner[i];
+            const double psis = 1.0 - (double)P.psif[i];
+            P.qc[i] = (own >= 0 && P.ptot[own] > 0.0) ? (T)(P.Q[own] * psis / P.ptot[own]) : T(0);
+            const Nbr o = make_nbr(s.x, s.y, s.z, S);
+            const uint8_t si = P.flags[i] & 1;
+            bool other = false;
+            for (int d = 0; d < kQ; ++d) {
+                if (d == kRest) continue;
+                if ((P.flags[i + offset_of(o, d)] & 1) != si) other = true;
+            }
+            bool part = psis > 0.0;
+            for (int d = 0; d < kQ && !part; ++d) part = vsq(d) == 1 && P.psif[i + offset_of(o, d)] < T(1);
+            // every box site is rewritten, so bits 1-3 are set from scratch
+            const uint8_t fl = (uint8_t)(si | (other ? (si ? 4 : 2) : 0) | (part ? 8 : 0));
+            P.flags[i] = fl;
+            listed = (fl & (1u | 2u | 8u)) != 0;
         }
-        bool part = psis > 0.0;
-        for (int d = 0; d < kQ && !part; ++d) part = vsq(d) == 1 && P.psif[i + offset_of(o, d)] < T(1);
-        // every box site is rewritten, so bits 1-3 are set from scratch
-        P.flags[i] = (uint8_t)(si | (other ? (si ? 4 : 2) : 0) | (part ? 8 : 0));
+        const unsigned long long all = __ballot(listed);
+        if (listed) {
+            const int lane = threadIdx.x & 63, first = __ffsll(all) - 1;
+            int at = 0;
+            if (lane == first) at = atomicAdd(P.npl, (int)__popcll(all));
+            at = __shfl(at, first, 64);
+            P.plist[at + __popcll(all & ((1ull << lane) - 1))] = (int32_t)i;
+        }
     }
 }
 
-// Pass 7: the particle-path sites (flag bits 0, 1 or 3), gathered from the boxes (each
-// site by the lowest-indexed box that holds it) into the context's list, in no particular
-// order: every such site lies in a box (a box reaches four sites beyond its sphere), and
-// the list kernels handle each listed site by itself.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_rp_list(Scalars S, Reproj<T> P) {
-    const int a = blockIdx.x;
-    const int B3 = S.rp_box * S.rp_box * S.rp_box;
-    for (int t = blockIdx.y * kBlock + threadIdx.x; t < B3; t += kBlock * gridDim.y) {
-        const BoxSite s = box_site(S, P.origin, a, t);
-        if ((P.flags[s.i] & (1u | 2u | 8u)) == 0 || first_box(S, P, a, s.x, s.y, s.z) != a) continue;
-        P.plist[atomicAdd(P.npl, 1)] = (int32_t)s.i;
-    }
+// Workgroups per box: one thread per box site while the chip is not full (2048 workgroups), at
+// least eight.
+unsigned box_groups(const Scalars& S, int np) {
+    const int B3 = S.rp_box * S.rp_box * S.rp_box, most = (B3 + kBlock - 1) / kBlock;
+    return (unsigned)std::min(most, std::max(8, (2048 + np - 1) / np));
 }
 
 template <typename T>
 void launch_reproject(const Scalars& S, const Fields<T>& F, const Reproj<T>& P, hipStream_t st) {
     if (P.np <= 0) return;
-    // the per-site passes split each box over a few workgroups (one per particle would
-    // leave most of the chip idle with a few hundred particles); the per-particle sums keep one
-    const int B3 = S.rp_box * S.rp_box * S.rp_box;
-    const dim3 g(P.np), gs(P.np, std::min(8, (B3 + 4 * kBlock - 1) / (4 * kBlock))), b(kBlock);
+    const unsigned groups = box_groups(S, P.np);
+    const dim3 g(P.np), gs(P.np, groups), b(kBlock);
     hipLaunchKernelGGL(k_rp_mark<T>, gs, b, 0, st, S, P);
     hipLaunchKernelGGL(k_rp_pairs<T>, g, dim3(64), 0, st, S, P);
     hipLaunchKernelGGL(k_rp_resolve<T>, gs, b, 0, st, S, P);
     hipLaunchKernelGGL(k_rp_convert<T>, gs, b, 0, st, S, F, P);
     hipLaunchKernelGGL(k_rp_ions<T>, gs, b, 0, st, S, F, P);
-    hipLaunchKernelGGL(k_rp_sum<T>, g, b, 0, st, S, P);
+    hipLaunchKernelGGL(k_rp_sum<T>, g, dim3(64), 0, st, S, P, (int)groups);
     hipLaunchKernelGGL(k_rp_finish<T>, gs, b, 0, st, S, P);
-    hipLaunchKernelGGL(k_rp_list<T>, gs, b, 0, st, S, P);
 }
 
 template void launch_reproject<float>(const Scalars&, const Fields<float>&, const Reproj<float>&, hipStream_t);
