@@ -1711,7 +1711,8 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
     // EK_POISSON_SITE_ORDER=1 keeps the multigrid solves in site order (a diagnostic switch:
     // the results are the same, bit for bit)
     const char* site_order = std::getenv("EK_POISSON_SITE_ORDER");
-    c->split_layout = !c->mg.empty() && !c->small && !c->gmg && !(site_order && std::atoi(site_order) != 0);
+    c->split_layout = !c->mg.empty() && !c->small && !c->gmg && columns_fit(S) &&
+                      !(site_order && std::atoi(site_order) != 0);
     // EK_POISSON_ONE_PASS=1 runs the lattice sweeps of colour-split solves in one pass
     // (k_sor_rb) where it fits.  The results are the same, bit for bit; on gfx950 the two
     // colour passes are faster (the one-pass kernel is bound by its FP64 rows, recomputed on

@@ -238,7 +238,9 @@ static ColumnGrid residual_grid(const Scalars& S) {
     return g;
 }
 
-bool columns_fit(const Scalars& S) { return S.nx % 2 == 0 && S.ny % 2 == 0 && S.nz % 2 == 0; }
+// Even axes, and a plane of a wave of pairs at least: a 2 x 2 x 2500 column would leave two threads of
+// a workgroup with 60 planes each.
+bool columns_fit(const Scalars& S) { return S.nx % 2 == 0 && S.ny % 2 == 0 && S.nz % 2 == 0 && S.nxy >= 128; }
 unsigned residual_col_blocks(const Scalars& S) { return residual_grid(S).blocks; }
 
 template <typename T>
