@@ -198,9 +198,11 @@ struct ek_ctx {
     double kms[EK_K_COUNT] = {0};      // timing level 3: per kernel
     long long kcnt[EK_K_COUNT] = {0};
     bool in_batch = false;  // owned by a batch: stepping goes through the batch
-    // pinned pieces through which large fields reach the host (copy_out), from the first such copy on
+    // large fields reach the host (copy_out) through pinned pieces on a stream of their own, both made
+    // by the first such copy; xfer_ev[kXferWorkers] marks the place in st behind which they are taken
     char* xfer = nullptr;
-    hipEvent_t xfer_ev[kXferWorkers] = {};
+    hipStream_t xfer_st = nullptr;
+    hipEvent_t xfer_ev[kXferWorkers + 1] = {};
     // reverse mode (periodic FP64 contexts): checkpoints of the last checkpointed forward
     // run and the adjoint fields
     struct {
@@ -2487,22 +2489,32 @@ extern "C" ek_status ek_autotune_multigrid(ek_ctx* c, int32_t trial_steps, int32
 // eight, 4.8 with pieces of 1 MiB); 16 MiB: 1.17 and 0.82; 6 MiB: 0.5 both ways, and the pinned
 // pieces cost 1 ms on first use.
 // Memory that is already pinned, or on a device, takes the plain copy.
+//
+// The threads use a stream of their own that waits for the context's: a context may run on
+// hipStreamPerThread, a handle that names another stream in every thread, so only the calling
+// thread may use it.
+static void xfer_release(ek_ctx* c) {
+    for (auto& e : c->xfer_ev) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+    if (c->xfer_st) (void)hipStreamDestroy(c->xfer_st);
+    if (c->xfer) (void)hipHostFree(c->xfer);
+    c->xfer_st = nullptr;
+    c->xfer = nullptr;
+}
+
 static bool xfer_ready(ek_ctx* c) {
     if (c->xfer) return true;
-    if (hipHostMalloc((void**)&c->xfer, kXferWorkers * kXferPiece, hipHostMallocDefault) != hipSuccess) {
+    bool ok = hipHostMalloc((void**)&c->xfer, kXferWorkers * kXferPiece, hipHostMallocDefault) == hipSuccess;
+    if (!ok) c->xfer = nullptr;
+    ok = ok && hipStreamCreateWithFlags(&c->xfer_st, hipStreamNonBlocking) == hipSuccess;
+    for (auto& e : c->xfer_ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
         (void)hipGetLastError();
-        c->xfer = nullptr;
-        return false;
+        xfer_release(c);
     }
-    for (int w = 0; w < kXferWorkers; ++w)
-        if (hipEventCreateWithFlags(&c->xfer_ev[w], hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            for (int v = 0; v < w; ++v) (void)hipEventDestroy(c->xfer_ev[v]);
-            (void)hipHostFree(c->xfer);
-            c->xfer = nullptr;
-            return false;
-        }
-    return true;
+    return ok;
 }
 
 static ek_status copy_out(ek_ctx* c, void* host, const void* dev, size_t bytes) {
@@ -2520,6 +2532,8 @@ static ek_status copy_out(ek_ctx* c, void* host, const void* dev, size_t bytes) 
         EK_HIP(hipStreamSynchronize(c->st));
         return EK_OK;
     }
+    EK_HIP(hipEventRecord(c->xfer_ev[kXferWorkers], c->st));
+    EK_HIP(hipStreamWaitEvent(c->xfer_st, c->xfer_ev[kXferWorkers], 0));
     const size_t head = (kXferPiece - (uintptr_t)host % kXferPiece) % kXferPiece;  // up to the first boundary
     const size_t n = (head > 0) + (bytes - head + kXferPiece - 1) / kXferPiece;
     std::mutex mu;
@@ -2535,8 +2549,8 @@ static ek_status copy_out(ek_ctx* c, void* host, const void* dev, size_t bytes) 
             hipError_t e;
             {
                 std::lock_guard<std::mutex> g(mu);  // the event follows its own copy
-                e = hipMemcpyAsync(slot, (const char*)dev + lo, hi - lo, hipMemcpyDeviceToHost, c->st);
-                if (e == hipSuccess) e = hipEventRecord(c->xfer_ev[w], c->st);
+                e = hipMemcpyAsync(slot, (const char*)dev + lo, hi - lo, hipMemcpyDeviceToHost, c->xfer_st);
+                if (e == hipSuccess) e = hipEventRecord(c->xfer_ev[w], c->xfer_st);
             }
             if (e == hipSuccess) e = hipEventSynchronize(c->xfer_ev[w]);
             if (e != hipSuccess) {
@@ -2562,7 +2576,7 @@ static ek_status copy_out(ek_ctx* c, void* host, const void* dev, size_t bytes) 
     }
     work(0);
     for (int w = 0; w < made; ++w) pool[w].join();
-    const hipError_t e = hipStreamSynchronize(c->st);
+    const hipError_t e = hipStreamSynchronize(c->xfer_st);
     EK_HIP((hipError_t)err.load());
     EK_HIP(e);
     return EK_OK;
@@ -2784,10 +2798,7 @@ extern "C" ek_status ek_destroy(ek_ctx* c) {
     for (auto e : c->pool) (void)hipEventDestroy(e);
     for (void* a : c->allocs) (void)hipFree(a);
     if (c->hscal) (void)hipHostFree(c->hscal);
-    if (c->xfer) {
-        for (auto e : c->xfer_ev) (void)hipEventDestroy(e);
-        (void)hipHostFree(c->xfer);
-    }
+    xfer_release(c);
     delete c;
     return EK_OK;
 }
