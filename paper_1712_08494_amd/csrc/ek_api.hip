@@ -2526,8 +2526,17 @@ static ek_status copy_out(ek_ctx* c, void* host, const void* dev, size_t bytes) 
         else if (a.type != hipMemoryTypeUnregistered)
             pieces = false;
     }
+    // (events and streams belong to the device that is current when they are made: a caller that has
+    // made another device current than the field's takes the plain copy too)
     int device = 0;
-    if (!pieces || hipGetDevice(&device) != hipSuccess || !xfer_ready(c)) {
+    if (pieces) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, dev) != hipSuccess || hipGetDevice(&device) != hipSuccess || a.device != device) {
+            (void)hipGetLastError();
+            pieces = false;
+        }
+    }
+    if (!pieces || !xfer_ready(c)) {
         EK_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, c->st));
         EK_HIP(hipStreamSynchronize(c->st));
         return EK_OK;

@@ -47,3 +47,19 @@ def test_reads_follow_the_steps_queued_before_them(precision):
     assert all(np.array_equal(got[k], want[k]) for k in want)
     a.close()
     b.close()
+
+
+def test_reads_with_another_device_current():
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    cfg, inp = wl.mixture_noise(shape=(128, 128, 80), precision="fp32")
+    cfg.poisson_tol = 1e-4
+    with torch.cuda.device(0):
+        sim = ek.EKSim(cfg, inp, stream=torch.cuda.Stream(0).cuda_stream)
+        sim.step(1)
+    with torch.cuda.device(1):
+        got = sim.field("phi")
+    with torch.cuda.device(0):
+        assert np.array_equal(got, sim.field("phi"))
+        sim.close()
