@@ -38,6 +38,15 @@ struct TimeRec {
 constexpr int kXferWorkers = 6;
 constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 
+// Residual that cycles with per-axis coarsening aim at, of the tolerance (FP64, FP32 contexts).
+// SOR, which these lattices took before, leaves a smaller error of phi at the same residual:
+// stopped just within 1e-10, the cycles left 3.7e-11 of phi at 50x37x29 in FP64 where SOR left 1.5e-12;
+// with 0.1 it is 5.5e-12, with 0.02 8.1e-13 (4x128x128: 5.1e-12 and 4.7e-12, now 1.4e-13).  An FP32
+// context's phi follows charges rounded to 6e-8 of themselves, so 0.1 of its 1e-8 is enough there
+// (1.1e-9).  The cost: 504 -> 632 us a step at 50x37x29 in FP64 (SOR 1487), 388 -> 476 at 4x128x128
+// (SOR 2805).
+constexpr double kAxisMargin[2] = {0.02, 0.1};
+
 // Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
 // from kCtl on the state of the single-workgroup solve.
 constexpr int kCtl = 32, kScal = kCtl + kCtlCount;
@@ -989,11 +998,16 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
             r = r_k0;
         }
         if (use_mg && r > target && !built) mg_build<T>(c, F);
-        while (use_mg && r > target && it < maxit) {
+        // Cycles with per-axis coarsening aim a margin below the tolerance.  Once within it they take
+        // one cycle more at most, so a tolerance near the rounding floor ends the solve too.
+        const double goal = c->gmg ? kAxisMargin[c->esz == 4] * target : target;
+        bool beyond = it == 0 && r <= target;  // a start within the tolerance is kept
+        while (use_mg && (r > target || (r > goal && !beyond)) && it < maxit) {
             int k = 1;
-            if (c->rate > 0.0 && c->rate < 1.0) k = (int)std::ceil(std::log(target / r) / std::log(c->rate));
+            if (r > target && c->rate > 0.0 && c->rate < 1.0) k = (int)std::ceil(std::log(goal / r) / std::log(c->rate));
             k = std::max(1, std::min(k, 8));
             k = std::min(k, maxit - it);
+            beyond = beyond || r <= target;
             {
                 Timer ts(c, EK_T_ITER, k);
                 EK_TRY(run_cycles<T>(c, FS, split, k));
@@ -1042,7 +1056,7 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
             need = 0;
         } else if (it > 0 && r > 0.0 && r < r0) {
             const double rho = std::pow(r / r0, 1.0 / it);
-            need = std::min(it, std::max(0, (int)std::ceil(std::log(target / r0) / std::log(rho) - 1e-9)));
+            need = std::min(it, std::max(0, (int)std::ceil(std::log(goal / r0) / std::log(rho) - 1e-9)));
         }
     }
     EK_HIP(hipGetLastError());
