@@ -38,7 +38,7 @@ struct TimeRec {
 constexpr int kXferWorkers = 6;
 constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 
-// Residual that cycles with per-axis coarsening aim at, of the tolerance (FP64, FP32 contexts).
+// Residual that solves with per-axis coarsening aim at, of the tolerance (FP64, FP32 contexts).
 // SOR, which these lattices took before, leaves a smaller error of phi at the same residual:
 // stopped just within 1e-10, the cycles left 3.7e-11 of phi at 50x37x29 in FP64 where SOR left 1.5e-12;
 // with 0.1 it is 5.5e-12, with 0.02 8.1e-13 (4x128x128: 5.1e-12 and 4.7e-12, now 1.4e-13).  An FP32
@@ -834,8 +834,8 @@ template <typename T>
 static void small_solve(ek_ctx* c, double tol, int maxit, bool step) {
     Timer tm(c, EK_T_POISSON);
     EK_KT(EK_K_TAIL);
-    const SmallArgs a{gmg_shape(c), tol, maxit, step ? c->fixed_cycles : 0, step ? 1 : 0, c->phi_history,
-                      c->phi_prev, c->phi_prev2, c->scal + kCtl};
+    const SmallArgs a{gmg_shape(c), tol, kAxisMargin[c->esz == 4], maxit, step ? c->fixed_cycles : 0, step ? 1 : 0,
+                      c->phi_history, c->phi_prev, c->phi_prev2, c->scal + kCtl};
     launch_small_solve<T>(c->S, fields<T>(c), c->gsub, gmg_tables(c), a, c->st);
 }
 

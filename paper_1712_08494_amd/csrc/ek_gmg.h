@@ -72,7 +72,7 @@ constexpr int kCtlRel0 = 0, kCtlOrder = 2, kCtlSince = 3, kCtlSteps = 4, kCtlNoC
 
 struct SmallArgs {
     GShape sh;
-    double tol;
+    double tol, margin;  // margin: see kAxisMargin
     int maxit, fixed;    // fixed > 0: that many cycles, no test
     int step, history;   // step: the start is extrapolated in time from phi, prev, prev2
     double *prev, *prev2, *ctl;

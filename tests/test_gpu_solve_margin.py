@@ -49,3 +49,22 @@ def test_error_of_phi(shape):
     st, it, rel = sim.poisson(1e-13, 1000)
     assert st == ek.EK_OK and phi_err(phi, sim.field("phi")) < 1e-11
     sim.close()
+
+
+# The solve in one workgroup: lattices down to a few sites, which coarsen once, and a long one whose cycles
+# contract least.  The start of a solve from the charge's own scale; bounds as above.
+@pytest.mark.parametrize("shape,walls", [((32, 1, 1), False), ((16, 2, 1), False), ((2, 1, 5), False), ((2, 5, 1), False),
+                                         ((4, 4, 2), False), ((2, 2, 10), True), ((2, 2, 300), False), ((2, 1, 4), False)])
+def test_single_workgroup_solves(shape, walls):
+    print(f"single-workgroup solve, error of phi, {shape}{' walls' if walls else ''}", flush=True)
+    cfg, inp = (wl.walls_interface if walls else wl.mixture_noise)(shape=shape, precision="fp64")
+    cfg.poisson_tol = 1e-10
+    cfg.eps_b = 3.0 * cfg.eps_a
+    sim = ek.EKSim(cfg, inp)
+    sim.step(20)
+    st, it, rel = sim.poisson(cfg.poisson_tol, 1000)
+    assert st == ek.EK_OK and rel <= cfg.poisson_tol / 3.0 and it <= 20
+    phi = sim.field("phi")
+    st, it, rel = sim.poisson(1e-13, 1000)
+    assert st == ek.EK_OK and phi_err(phi, sim.field("phi")) < 1e-11
+    sim.close()
