@@ -45,6 +45,8 @@ constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 // context's phi follows charges rounded to 6e-8 of themselves, so 0.1 of its 1e-8 is enough there
 // (1.1e-9).  The cost: 504 -> 632 us a step at 50x37x29 in FP64 (SOR 1487), 388 -> 476 at 4x128x128
 // (SOR 2805).
+// Lattices that the halving cycle covers too (ek_ctx::mg) keep the tolerance as it is: that cycle
+// stopped just within it and left no less (8.2e-11 at 40x36x24 in FP64, the per-axis one 4.7e-11).
 constexpr double kAxisMargin[2] = {0.02, 0.1};
 
 // Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
@@ -700,6 +702,8 @@ static void vcycle(ek_ctx* c, const Fields<T>& F0, bool split) {
     }
 }
 
+static double axis_margin(const ek_ctx* c) { return c->mg.empty() ? kAxisMargin[c->esz == 4] : 1.0; }
+
 static GTab gmg_tables(const ek_ctx* c) { return GTab{c->gt_pn, c->gt_w, c->gt_first, c->gt_ratio}; }
 
 // The shape of a hierarchy with per-axis coarsening: one more sweep before the correction on
@@ -834,7 +838,7 @@ template <typename T>
 static void small_solve(ek_ctx* c, double tol, int maxit, bool step) {
     Timer tm(c, EK_T_POISSON);
     EK_KT(EK_K_TAIL);
-    const SmallArgs a{gmg_shape(c), tol, kAxisMargin[c->esz == 4], maxit, step ? c->fixed_cycles : 0, step ? 1 : 0,
+    const SmallArgs a{gmg_shape(c), tol, axis_margin(c), maxit, step ? c->fixed_cycles : 0, step ? 1 : 0,
                       c->phi_history, c->phi_prev, c->phi_prev2, c->scal + kCtl};
     launch_small_solve<T>(c->S, fields<T>(c), c->gsub, gmg_tables(c), a, c->st);
 }
@@ -1000,7 +1004,7 @@ static ek_status poisson_solve(ek_ctx* c, double tol, int maxit, int* iters_out,
         if (use_mg && r > target && !built) mg_build<T>(c, F);
         // Cycles with per-axis coarsening aim a margin below the tolerance.  Once within it they take
         // one cycle more at most, so a tolerance near the rounding floor ends the solve too.
-        const double goal = c->gmg ? kAxisMargin[c->esz == 4] * target : target;
+        const double goal = c->gmg ? axis_margin(c) * target : target;
         bool beyond = it == 0 && r <= target;  // a start within the tolerance is kept
         while (use_mg && (r > target || (r > goal && !beyond)) && it < maxit) {
             int k = 1;
@@ -1530,6 +1534,31 @@ static ek_status init_impl(ek_ctx* c, const double* rho_a, const double* rho_b, 
 
 // Checks the parameters and sets up the context's scalars and multigrid levels: host work
 // only, no device call.
+// Whether the halving cycle's coarsest grid, ten SOR sweeps in one workgroup, costs more than it
+// saves against coarsening by axis, whose lattice passes are the slower site-order ones.  Halving ->
+// per axis, us a step in FP32 / in FP64:
+//   - up to 16 cells a side ten sweeps do;
+//   - walls, z short: lateral modes are weak, and the layers between walls (a multiple of four less
+//     two) coarsen unevenly: 128x16x16 270 -> 425 / 344 -> 579, 120x48x48 621 -> 802 / 872 -> 1208; only
+//     a coarsest grid of some 4000 cells under a small lattice costs more (36x32x32 810 -> 483 / 1151 -> 672,
+//     40x36x24 551 -> 514 / 753 -> 699);
+//   - walls, z long: the charged walls drive the modes that the sweeps miss: 8x8x128 715 -> 270 /
+//     1203 -> 376, 80x80x160 1190 -> 1061 / 1984 -> 1662; in FP32 the lattice passes outweigh a side of
+//     18 from two million sites on (96x96x288 1556 -> 1681 / 2899 -> 2662);
+//   - periodic: up to 131 072 sites the coarsest grid weighs more (36x32x32 340 -> 264 / 515 -> 371,
+//     8x128x128 384 -> 328 / 697 -> 469).  Above, the lattice passes do (16x144x144 345 -> 377 / 510 -> 559,
+//     288x256x256 6119 -> 7707 / 11097 -> 13484), or the gain is bought with accuracy (72x64x64 490 -> 432 /
+//     690 -> 638, but 5.1e-11 -> 2.6e-10 of phi at a residual of 1e-10), until the cycles grow: a side of 64
+//     in FP64 up to a million sites (1024x32x32 545 -> 658 / 1260 -> 977), of 128 always (2048x32x32
+//     1594 -> 974 / 4888 -> 1581).
+static bool coarsest_costs(const MGLevel& B, unsigned N, bool walls, bool fp64) {
+    const int side = std::max(B.nx, std::max(B.ny, B.nz));
+    if (side <= 16) return false;
+    if (walls && B.nz <= 16) return B.n >= 4000 && N <= 65536;
+    if (walls) return B.nz >= 32 || fp64 || N <= (1u << 21);
+    return side > (fp64 && N <= (1u << 20) ? 32 : 64) || N <= (1u << 17);
+}
+
 static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* parts, int32_t n_parts) {
     if (!p) return fail(c, EK_EINVAL, "null parameters");
     c->p = *p;
@@ -1696,12 +1725,11 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
         c->gsub = gmg_sub(c->gh, 0, true);
         c->small = gmg_small_fits(c->gsub, S.ndomain);
         // Larger lattices whose axes do not halve far enough: no V-cycle above (the automatic
-        // choice took SOR: 110 sweeps a step on 50x37x29, 319 on 4x128x128), or one whose
-        // coarsest grid is longer than ten SOR sweeps reach (13 cycles a step on 8x8x48).
+        // choice took SOR: 110 sweeps a step on 50x37x29, 319 on 4x128x128), or one whose coarsest
+        // grid costs more than the column kernels that only the halving cycle has.
         const int axis = std::max(dims[0], std::max(dims[1], dims[2]));
-        const bool long_coarsest = !c->mg.empty() && std::max(c->mg.back().nx, std::max(c->mg.back().ny, c->mg.back().nz)) > 16;
         const int first = gmg_tail_first(c->gh);
-        if (!c->small && (c->mg.empty() || long_coarsest) && axis <= 65535 && first >= 0) {
+        if (!c->small && (c->mg.empty() || coarsest_costs(c->mg.back(), S.N, S.walls, c->esz == 8)) && axis <= 65535 && first >= 0) {
             c->gmg = true;
             c->gsub = gmg_sub(c->gh, first, false);
             for (int l = 0; l <= first; ++l) {
