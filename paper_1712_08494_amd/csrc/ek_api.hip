@@ -42,12 +42,12 @@ constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 // SOR, which these lattices took before, leaves a smaller error of phi at the same residual:
 // stopped just within 1e-10, the cycles left 3.7e-11 of phi at 50x37x29 in FP64 where SOR left 1.5e-12;
 // with 0.1 it is 5.5e-12, with 0.02 8.1e-13 (4x128x128: 5.1e-12 and 4.7e-12, now 1.4e-13).  An FP32
-// context's phi follows charges rounded to 6e-8 of themselves, so 0.1 of its 1e-8 is enough there
-// (1.1e-9).  The cost: 504 -> 632 us a step at 50x37x29 in FP64 (SOR 1487), 388 -> 476 at 4x128x128
+// context's phi follows charges rounded to 6e-8 of themselves, so 0.3 of its 1e-8 is enough there
+// (1.2e-8 -> 1.7e-9 at 50x37x29, 355 -> 386 us a step; 0.1: 1.1e-9, 423 us).  The cost in FP64: 504 -> 632 us a step at 50x37x29 in FP64 (SOR 1487), 388 -> 476 at 4x128x128
 // (SOR 2805).
 // Lattices that the halving cycle covers too (ek_ctx::mg) keep the tolerance as it is: that cycle
 // stopped just within it and left no less (8.2e-11 at 40x36x24 in FP64, the per-axis one 4.7e-11).
-constexpr double kAxisMargin[2] = {0.02, 0.1};
+constexpr double kAxisMargin[2] = {0.02, 0.3};
 
 // Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
 // from kCtl on the state of the single-workgroup solve.
