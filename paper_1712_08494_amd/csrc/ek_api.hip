@@ -208,6 +208,7 @@ struct ek_ctx {
     long long tcnt[EK_T_COUNT] = {0};
     double kms[EK_K_COUNT] = {0};      // timing level 3: per kernel
     long long kcnt[EK_K_COUNT] = {0};
+    bool batched = false;   // made for a batch, whose cycles are the halving ones: so are its own solves
     bool in_batch = false;  // owned by a batch: stepping goes through the batch
     // large fields reach the host (copy_out) through pinned pieces on a stream of their own, both made
     // by the first such copy; xfer_ev[kXferWorkers] marks the place in st behind which they are taken
@@ -1718,7 +1719,7 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
     // solved there by one launch: below that size every launch of a cycle is latency.  At the
     // upper end 16^3 takes 152 us per step there against 268 with launches; a 4x4x128 column,
     // whose coarsest launched grid (2x2x64) ten sweeps do not solve, 106 against 2840.
-    if (p->poisson_solver != EK_POISSON_SOR && !c->fft) {
+    if (p->poisson_solver != EK_POISSON_SOR && !c->fft && !c->batched) {
         const int dims[3] = {S.nx, S.ny, S.z1 - S.z0 + 1};
         const bool per[3] = {true, true, !S.walls};
         gmg_hierarchy(dims, per, c->gh);
@@ -1773,15 +1774,22 @@ static ek_status init_dispatch(ek_ctx* c, const double* rho_a, const double* rho
     return init_impl<double>(c, rho_a, rho_b, n_plus, n_minus, parts, n_parts);
 }
 
+static ek_status init_ctx(const ek_params* p, const double* rho_a, const double* rho_b, const double* n_plus,
+                          const double* n_minus, const ek_particle* parts, int32_t n_parts, hipStream_t stream,
+                          bool batched, ek_ctx** out) {
+    ek_ctx* c = new ek_ctx();
+    *out = c;
+    c->st = stream;
+    c->batched = batched;
+    EK_TRY(configure(c, p, parts, n_parts));
+    return init_dispatch(c, rho_a, rho_b, n_plus, n_minus, parts, n_parts);
+}
+
 extern "C" ek_status ek_init(const ek_params* p, const double* rho_a, const double* rho_b, const double* n_plus,
                              const double* n_minus, const ek_particle* parts, int32_t n_parts, void* stream,
                              ek_ctx** out) {
     if (!out) return EK_EINVAL;
-    ek_ctx* c = new ek_ctx();
-    *out = c;
-    c->st = (hipStream_t)stream;
-    EK_TRY(configure(c, p, parts, n_parts));
-    return init_dispatch(c, rho_a, rho_b, n_plus, n_minus, parts, n_parts);
+    return init_ctx(p, rho_a, rho_b, n_plus, n_minus, parts, n_parts, (hipStream_t)stream, false, out);
 }
 
 extern "C" ek_status ek_workspace_bytes(const ek_params* p, const ek_particle* parts, int32_t n_parts, size_t* bytes) {
@@ -3092,7 +3100,7 @@ extern "C" ek_status ek_batch_init(const ek_params* params, int32_t n_rep, const
             return EK_EINVAL;
         }
         ek_ctx* c = nullptr;
-        ek_status s = ek_init(&p, rho_a[r], rho_b[r], n_plus[r], n_minus[r], nullptr, 0, b->st, &c);
+        ek_status s = init_ctx(&p, rho_a[r], rho_b[r], n_plus[r], n_minus[r], nullptr, 0, b->st, true, &c);
         if (s != EK_OK) {
             b->err = "replica " + std::to_string(r) + ": " + (c ? c->err : std::string("init failed"));
             if (c) ek_destroy(c);
