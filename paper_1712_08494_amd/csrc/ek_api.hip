@@ -1295,14 +1295,9 @@ static ek_status allocate_all(ek_ctx* c, const HostGeom& g, int np) {
     EK_TRY(dalloc(c, (void**)&c->obs_max, 16 * sizeof(int)));
     EK_TRY(dalloc(c, (void**)&c->stage, (size_t)N * 8));
     EK_TRY(dalloc(c, (void**)&c->stage2, (size_t)N * 8));
-    for (auto& L : c->mg) {
-        EK_TRY(dalloc(c, (void**)&L.phi, (size_t)L.n * 8));
-        EK_TRY(dalloc(c, (void**)&L.s, (size_t)L.n * 8));
-        EK_TRY(dalloc(c, (void**)&L.ax, (size_t)L.n * 8));
-        EK_TRY(dalloc(c, (void**)&L.ay, (size_t)L.n * 8));
-        EK_TRY(dalloc(c, (void**)&L.az, (size_t)L.n * 8));
-    }
-    for (auto& L : c->gm) {
+    // the grids that the cycle runs on: those coarsened by axis, the halving ones, or none of
+    // them (in one workgroup they are in LDS)
+    for (auto& L : c->small || c->gmg ? c->gm : c->mg) {
         EK_TRY(dalloc(c, (void**)&L.phi, (size_t)L.n * 8));
         EK_TRY(dalloc(c, (void**)&L.s, (size_t)L.n * 8));
         EK_TRY(dalloc(c, (void**)&L.ax, (size_t)L.n * 8));
@@ -1413,7 +1408,8 @@ static ek_status init_impl(ek_ctx* c, const double* rho_a, const double* rho_b, 
     c->phi_own = c->phi;
     c->q_own = c->q;
     EK_HIP(hipHostMalloc((void**)&c->hscal, kScal * sizeof(double), hipHostMallocDefault));
-    for (auto& L : c->mg) EK_HIP(hipMemsetAsync(L.phi, 0, (size_t)L.n * 8, c->st));
+    for (auto& L : c->mg)
+        if (L.phi) EK_HIP(hipMemsetAsync(L.phi, 0, (size_t)L.n * 8, c->st));
     for (int b = 0; b < 2; ++b)
         for (int k = 0; k < 2; ++k) {
             if (c->f[b][k]) EK_HIP(hipMemsetAsync(c->f[b][k], 0, (size_t)kQ * N * es, c->st));
