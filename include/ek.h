@@ -185,8 +185,9 @@ typedef struct ek_obs {
 #define EK_T_FUSED 3     /* fused ion update + force + collide + stream pass */
 #define EK_T_PARTICLE 4  /* particle force sums and integration */
 #define EK_T_ITER 5      /* Poisson iterations: SOR sweep chunks (count = sweeps) or V-cycles (count = cycles) */
-#define EK_T_SMOOTH 6    /* red-black colour passes on the lattice itself (SOR or multigrid smoothing): one event
-                            pair per group of back-to-back passes, count = passes */
+#define EK_T_SMOOTH 6    /* colour passes on the lattice itself (SOR or multigrid smoothing): one event pair per
+                            group of back-to-back passes, count = passes.  Where one workgroup solves the
+                            lattice in one launch, this and EK_T_ITER are taken by the device's clock inside it */
 #define EK_T_COUNT 7
 
 /* Single kernels timed at timing level 3 (ek_kernel_name gives each one's name). */
@@ -202,14 +203,14 @@ typedef struct ek_obs {
 #define EK_K_RESTRICT_FINE 9
 #define EK_K_RESTRICT 10
 #define EK_K_SMOOTH 11           /* colour pass on a launched coarse grid */
-#define EK_K_TAIL 12             /* single-workgroup solve of the two smallest grids */
+#define EK_K_TAIL 12             /* single-workgroup solve of the smallest grids, or of a whole small lattice */
 #define EK_K_PROLONG_RED_FINE 13
 #define EK_K_PROLONG_FINE 14
 #define EK_K_PROLONG 15
 #define EK_K_FINALIZE 16
 #define EK_K_FORCE 17
 #define EK_K_FUSED 18
-#define EK_K_PARTICLE 19         /* particle forces and integration */
+#define EK_K_PARTICLE 19         /* particle forces and integration (moving particles: two launches as one) */
 #define EK_K_LAGGED 20           /* a whole lagged Fourier solve (right-hand side, transforms, division) */
 #define EK_K_REPROJECT 21        /* projection of moving particles after their step (reproject) */
 #define EK_K_SOR_RB 22           /* one whole red-black lattice sweep in one pass (colour-split solves) */

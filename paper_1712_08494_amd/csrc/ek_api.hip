@@ -50,8 +50,8 @@ constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 constexpr double kAxisMargin[2] = {0.02, 0.3};
 
 // Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
-// from kCtl on the state of the single-workgroup solve.
-constexpr int kCtl = 32, kScal = kCtl + kCtlCount;
+// from kCtl on the state of the single-workgroup solve, from kClk on its clock.
+constexpr int kCtl = 32, kClk = kCtl + kCtlCount, kScal = kClk + kClkCount;
 
 struct ek_ctx {
     ek_params p{};
@@ -840,7 +840,8 @@ static void small_solve(ek_ctx* c, double tol, int maxit, bool step) {
     Timer tm(c, EK_T_POISSON);
     EK_KT(EK_K_TAIL);
     const SmallArgs a{gmg_shape(c), tol, axis_margin(c), maxit, step ? c->fixed_cycles : 0, step ? 1 : 0,
-                      c->phi_history, c->phi_prev, c->phi_prev2, c->scal + kCtl};
+                      c->phi_history, c->phi_prev, c->phi_prev2, c->scal + kCtl,
+                      c->timing == 1 || c->timing == 2 ? c->scal + kClk : nullptr};
     launch_small_solve<T>(c->S, fields<T>(c), c->gsub, gmg_tables(c), a, c->st);
 }
 
@@ -2814,6 +2815,7 @@ extern "C" ek_status ek_set_timing(ek_ctx* c, int32_t enable) {
         c->kms[k] = 0.0;
         c->kcnt[k] = 0;
     }
+    if (c->small && c->phi) EK_HIP(hipMemsetAsync(c->scal + kClk, 0, kClkCount * sizeof(double), c->st));
     return EK_OK;
 }
 
@@ -2827,6 +2829,20 @@ extern "C" ek_status ek_get_timing(ek_ctx* c, ek_timing* out) {
     for (int k = 0; k < EK_K_COUNT; ++k) {
         out->kernel_ms[k] = c->kms[k];
         out->kernel_count[k] = c->kcnt[k];
+    }
+    if (c->small && c->phi && (c->timing == 1 || c->timing == 2)) {  // the cycles inside its one launch
+        double h[kClkCount];
+        int dev = 0, khz = 0;
+        EK_HIP(hipMemcpyAsync(h, c->scal + kClk, sizeof(h), hipMemcpyDeviceToHost, c->st));
+        EK_HIP(hipStreamSynchronize(c->st));
+        EK_HIP(hipGetDevice(&dev));
+        EK_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+        out->ms[EK_T_ITER] = h[kClkIter] / khz;
+        out->count[EK_T_ITER] = (int64_t)h[kClkCycles];
+        if (c->timing == 2) {
+            out->ms[EK_T_SMOOTH] = h[kClkSmooth] / khz;
+            out->count[EK_T_SMOOTH] = (int64_t)h[kClkPasses];
+        }
     }
     return EK_OK;
 }

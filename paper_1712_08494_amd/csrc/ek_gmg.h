@@ -70,12 +70,17 @@ struct GShape {
 constexpr int kCtlRel0 = 0, kCtlOrder = 2, kCtlSince = 3, kCtlSteps = 4, kCtlNoConv = 5, kCtlIters = 6, kCtlTotal = 7,
               kCtlRel = 8, kCtlRelStart = 9, kCtlRelMax = 10, kCtlCount = 11;
 
+// Times taken inside the single-workgroup solve, in ticks of the device's wall clock: its cycles, and the
+// lattice sweeps in them, with their numbers.
+constexpr int kClkIter = 0, kClkCycles = 1, kClkSmooth = 2, kClkPasses = 3, kClkCount = 4;
+
 struct SmallArgs {
     GShape sh;
     double tol, margin;  // margin: see kAxisMargin
     int maxit, fixed;    // fixed > 0: that many cycles, no test
     int step, history;   // step: the start is extrapolated in time from phi, prev, prev2
     double *prev, *prev2, *ctl;
+    double* clock;       // adds to kClk*, or null
 };
 template <typename T>
 void launch_small_solve(const Scalars& S, const Fields<T>& F, const GSub& G, const GTab& t, const SmallArgs& a,

@@ -519,7 +519,8 @@ __device__ __forceinline__ double wg_sum(double v, double* sm, int tid, int nt) 
 // here: 25 us for the coarse grids and the inverse, 5 cycles of 12 us), against 2850 us
 // with launched cycles; of 16^3 in FP64 152 against 268 us.
 // ------------------------------------------------------------------------------------
-template <typename T, int NS, int NT>
+// CLK: with its clock (a kernel of its own: the ticks cost the other one registers).
+template <typename T, int NS, int NT, bool CLK>
 __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub G, GTab tab, SmallArgs P) {
     extern __shared__ __align__(16) char lds_raw[];
     const int tid = threadIdx.x;
@@ -678,7 +679,9 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
             }
         return wg_sum(rr, A.sum, tid, nt);
     };
+    long long smoothing = 0;  // ticks in the lattice sweeps
     auto sweeps = [&](int n) __attribute__((always_inline)) {
+        const long long t0 = CLK ? wall_clock64() : 0;
         for (int s = 0; s < n; ++s)
             for (int c = 0; c < S.ncolor; ++c) {
 #pragma unroll
@@ -689,6 +692,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
                     }
                 __syncthreads();
             }
+        if (CLK) smoothing += wall_clock64() - t0;
     };
 
     const double rr0 = residual();  // (its barriers: every thread is past the reads of eps)
@@ -700,6 +704,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
     // tolerance add up to 2e-9 of the density.  A second one follows where the first does not reach
     // the margin of the launched cycles (2x2x300 in FP64: 7.5e-12 of phi after one, SOR 3.1e-12).
     int it = 0, beyond = 0;
+    const long long started = CLK ? wall_clock64() : 0;
     while (ss > 0.0 && it < most && rr < 1e300) {  // (not finite: no cycle can mend it)
         if (P.fixed == 0 && rr <= stop) {
             if (it == 0 || beyond == 2 || (beyond == 1 && rr <= deep)) break;
@@ -721,6 +726,12 @@ __global__ __launch_bounds__(NT) void k_small_solve(Scalars S, Fields<T> F, GSub
         sweeps(P.sh.fine_post);
         rr = residual();
         ++it;
+    }
+    if (CLK && tid == 0) {
+        P.clock[kClkIter] += (double)(wall_clock64() - started);
+        P.clock[kClkCycles] += it;
+        P.clock[kClkSmooth] += (double)smoothing;
+        P.clock[kClkPasses] += (double)it * (P.sh.fine_pre + P.sh.fine_post) * S.ncolor;
     }
 
     // gauge mean(phi) = 0 and the wall layers (Gauss's law at the charged wall faces)
@@ -777,12 +788,13 @@ void launch_small_solve(const Scalars& S, const Fields<T>& F, const GSub& G, con
     // 2048 sites twice the threads (128 registers, a few spills) beat twice the rows (16^3 in
     // FP64: 152 against 156 us per step, 14 x 17 x 15 in FP32: 185 against 206).
     auto go = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(1), dim3(nt), lds, st, S, F, G, t, a); };
+    const bool clk = a.clock != nullptr;
     if (S.ndomain <= 1024)
-        go(k_small_solve<T, 2, 512>, 512);
+        clk ? go(k_small_solve<T, 2, 512, true>, 512) : go(k_small_solve<T, 2, 512, false>, 512);
     else if (S.ndomain <= 2048)
-        go(k_small_solve<T, 4, 512>, 512);
+        clk ? go(k_small_solve<T, 4, 512, true>, 512) : go(k_small_solve<T, 4, 512, false>, 512);
     else
-        go(k_small_solve<T, 4, 1024>, 1024);
+        clk ? go(k_small_solve<T, 4, 1024, true>, 1024) : go(k_small_solve<T, 4, 1024, false>, 1024);
 }
 
 // ------------------------------------------------------------------------------------
