@@ -46,7 +46,8 @@ typedef int32_t ek_status;
 #define EK_ESTATE (-6)     /* call not valid in the context's current state */
 
 #define EK_POISSON_AUTO 0 /* multigrid: axes halved while all divide by 4, or each axis coarsened by itself where that
-                             stops too early (odd or short axes, lattices solved in one workgroup) */
+                             stops too early (odd or short axes), leaves a costly coarsest grid, or the lattice is
+                             solved in one workgroup */
 #define EK_POISSON_SOR 1  /* red-black successive over-relaxation */
 #define EK_POISSON_MG 2   /* the same, EINVAL unless every axis divides by 4 (and the coarsest grid is small) */
 #define EK_POISSON_FFT 3  /* the lagged Fourier scheme of Sec. II D, periodic lattices only: each step solves
@@ -81,8 +82,9 @@ typedef struct ek_params {
     double E_ext[3];            /* uniform external field */
     double body_accel[3];       /* uniform body acceleration g (force density rho g) */
     double sigma_wall[2];       /* surface charge density of the z = 0 and z = nz-1 walls */
-    double poisson_tol;         /* relative residual ||r||_2 <= tol ||s||_2 of the Poisson solve */
-    double sor_omega;           /* over-relaxation factor; <= 0: chosen from the lattice size */
+    double poisson_tol;         /* relative residual ||r||_2 <= tol ||s||_2 of the Poisson solve (solves with
+                                   per-axis coarsening aim a few times below it) */
+    double sor_omega;           /* over-relaxation factor of SOR solves; <= 0: chosen from the lattice size */
     double particle_rho;        /* particle mass density (mass = rho_p 4/3 pi r^3) */
     double k_hertz;             /* Hertz contact stiffness */
     double eta;                 /* dynamic viscosity used by the lubrication force */
@@ -114,7 +116,8 @@ typedef struct ek_params {
                                    and end residuals stay on the device and ek_observables reports them
                                    (poisson_rel, poisson_rel0, and poisson_rel_max, the largest since its last
                                    call).  The warm start is then linear in time unless phi_history is set.
-                                   Multigrid contexts only (EK_EINVAL otherwise).  ek_poisson and the solve of
+                                   Lattices whose axes halve only (every axis divisible by 4 and a coarsest
+                                   grid of at most 4608 cells; EK_EINVAL otherwise).  ek_poisson and the solve of
                                    ek_init always run to the tolerance */
     int32_t fp32_plain_collision; /* FP32 populations: 0 (default) makes the collision conserve each site's
                                    mass exactly: the moments pass sums the populations in FP64, and the rest
@@ -362,7 +365,8 @@ int32_t ek_autotune_candidates(int32_t* shapes, double* omegas);
    each candidate's mean milliseconds per step.  Device memory: a copy of the state
    (about (2 x 19 + 2) N element sizes + 24 N bytes), held only during the call.  The Poisson
    tolerance of the context applies; a solve that stops at maxit counts with its time.
-   Synchronises.  Errors: EK_EINVAL (trial_steps outside 1..1000, a context solved by SOR),
+   Synchronises.  Errors: EK_EINVAL (trial_steps outside 1..1000, a lattice whose axes do not halve, as for
+   ek_params.poisson_cycles),
    EK_ESTATE (replica of a batch), EK_ENOMEM, EK_EHIP; on an error the shape in place
    before the call is kept. */
 ek_status ek_autotune_multigrid(struct ek_ctx* ctx, int32_t trial_steps, int32_t* best, double* ms_per_step);
@@ -395,7 +399,11 @@ ek_status ek_observables_device(struct ek_ctx* ctx, double* d_out);
 /* Copy one field of the current state to host memory (nx*ny*nz doubles): the fluid and ion
    densities, potential, pre-force velocity (Sec. II A-D), charge and permittivity (eqs.
    electric_potential, dielectric_constant), solid fraction and mask (Sec. II E) or the field
-   E = -grad phi + E_ext.  Synchronises. */
+   E = -grad phi + E_ext.  Synchronises.  Reads of 8 MiB or more (ek_get_populations and the fields
+   of ek_observables too) into pageable memory are copied by the calling thread and up to five
+   helpers that live as long as the call; the first one pins 12 MiB of host memory and makes a
+   stream, which the context keeps until ek_destroy.  Pinned or device destinations are
+   copied directly. */
 ek_status ek_get_field(struct ek_ctx* ctx, int32_t field, double* host_out);
 
 /* (Sec. II A) Copy the populations of component comp (0 = a, 1 = b) to host memory as

@@ -1709,7 +1709,7 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
     if (p->fp32_plain_collision != 0 && p->fp32_plain_collision != 1)
         return fail(c, EK_EINVAL, "fp32_plain_collision must be 0 or 1");
     if (p->poisson_cycles > 0 && (c->mg.empty() || c->fft))
-        return fail(c, EK_EINVAL, "a fixed V-cycle count needs the multigrid solver");
+        return fail(c, EK_EINVAL, "a fixed V-cycle count needs V-cycles on axes that halve (every axis divisible by 4, a coarsest grid of at most 4608 cells)");
     c->fixed_cycles = p->poisson_cycles;
     c->esz = p->precision == EK_FP32 ? 4 : 8;
     // A lattice of at most 4096 sites that fits one workgroup's LDS with its coarse grids is
@@ -2516,7 +2516,7 @@ extern "C" int32_t ek_autotune_candidates(int32_t* shapes, double* omegas) {
 extern "C" ek_status ek_autotune_multigrid(ek_ctx* c, int32_t trial_steps, int32_t* best, double* ms_per_step) {
     if (!c || !c->phi) return EK_ESTATE;
     if (c->in_batch) return fail(c, EK_ESTATE, "replica of a batch: its cycle is fixed by the batch");
-    if (c->mg.empty()) return fail(c, EK_EINVAL, "the axes of this lattice do not halve: there is no V-cycle to tune");
+    if (c->mg.empty()) return fail(c, EK_EINVAL, "the axes of this lattice do not halve (every axis divisible by 4, a coarsest grid of at most 4608 cells): its V-cycle is not tuned");
     if (c->fft) return fail(c, EK_EINVAL, "the lagged Fourier scheme runs no V-cycles in its steps");
     if (c->S.reproject) return fail(c, EK_EINVAL, "moving particles change the geometry, which the tuner does not restore");
     if (trial_steps < 1 || trial_steps > 1000) return fail(c, EK_EINVAL, "trial_steps must be in 1..1000");
