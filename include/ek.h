@@ -82,8 +82,8 @@ typedef struct ek_params {
     double E_ext[3];            /* uniform external field */
     double body_accel[3];       /* uniform body acceleration g (force density rho g) */
     double sigma_wall[2];       /* surface charge density of the z = 0 and z = nz-1 walls */
-    double poisson_tol;         /* relative residual ||r||_2 <= tol ||s||_2 of the Poisson solve (solves with
-                                   per-axis coarsening aim a few times below it) */
+    double poisson_tol;         /* relative residual ||r||_2 <= tol ||s||_2 of the Poisson solve (FP64
+                                   solves with per-axis coarsening aim well below it) */
     double sor_omega;           /* over-relaxation factor of SOR solves; <= 0: chosen from the lattice size */
     double particle_rho;        /* particle mass density (mass = rho_p 4/3 pi r^3) */
     double k_hertz;             /* Hertz contact stiffness */

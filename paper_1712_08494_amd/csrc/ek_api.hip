@@ -38,16 +38,17 @@ struct TimeRec {
 constexpr int kXferWorkers = 6;
 constexpr size_t kXferPiece = (size_t)2 << 20, kXferLeast = (size_t)8 << 20;
 
-// Residual that solves with per-axis coarsening aim at, of the tolerance (FP64, FP32 contexts).
-// SOR, which these lattices took before, leaves a smaller error of phi at the same residual:
-// stopped just within 1e-10, the cycles left 3.7e-11 of phi at 50x37x29 in FP64 where SOR left 1.5e-12;
-// with 0.1 it is 5.5e-12, with 0.02 8.1e-13 (4x128x128: 5.1e-12 and 4.7e-12, now 1.4e-13).  An FP32
-// context's phi follows charges rounded to 6e-8 of themselves, so 0.3 of its 1e-8 is enough there
-// (1.2e-8 -> 1.7e-9 at 50x37x29, 355 -> 386 us a step; 0.1: 1.1e-9, 423 us).  The cost in FP64: 504 -> 632 us a step at 50x37x29 in FP64 (SOR 1487), 388 -> 476 at 4x128x128
-// (SOR 2805).
-// Lattices that the halving cycle covers too (ek_ctx::mg) keep the tolerance as it is: that cycle
-// stopped just within it and left no less (8.2e-11 at 40x36x24 in FP64, the per-axis one 4.7e-11).
-constexpr double kAxisMargin[2] = {0.02, 0.3};
+// Residual that FP64 solves with per-axis coarsening aim at, of the tolerance, on lattices that SOR solved
+// before.  SOR leaves a smaller error of phi at the same residual.  Largest relative error of a field
+// against 64-bit solutions after 20 steps, SOR / stopped at the tolerance / 0.1 of it / 0.02 of it:
+//   mixture 50x37x29   6.3e-12  8.5e-11  1.1e-11  1.5e-12     colloids 44^3       3.2e-12  1.3e-11  1.5e-12  1.7e-13
+//   mixture 70^3       4.1e-12  4.6e-11  8.3e-12  1.5e-12     walls 50x37x29      2.2e-13  2.9e-12  6.8e-13  5.5e-14
+//   drop 4x128x128     7.2e-13  4.5e-12  2.8e-13  1.7e-14     reverse mode 52^3   9.3e-14  1.8e-12  1.8e-13  1.6e-13
+// (mixture 50x37x29: 25.3, 9.6, 11.0 and 12.3 ms for the 20 steps).  An FP32 context's error is its
+// rounding's, 1e-7, all the same.  Lattices that the halving cycle covers too (ek_ctx::mg) keep the tolerance as
+// it is: that cycle stopped just within it and left no less (8.2e-11 of phi at 40x36x24, the per-axis one
+// 4.7e-11).
+constexpr double kAxisMargin = 0.02;
 
 // Device scalars of a context (ek_ctx::scal) and their host mirror: [0..31] sums and residuals,
 // from kCtl on the state of the single-workgroup solve, from kClk on its clock.
@@ -703,7 +704,7 @@ static void vcycle(ek_ctx* c, const Fields<T>& F0, bool split) {
     }
 }
 
-static double axis_margin(const ek_ctx* c) { return c->mg.empty() ? kAxisMargin[c->esz == 4] : 1.0; }
+static double axis_margin(const ek_ctx* c) { return c->mg.empty() && c->esz == 8 ? kAxisMargin : 1.0; }
 
 static GTab gmg_tables(const ek_ctx* c) { return GTab{c->gt_pn, c->gt_w, c->gt_first, c->gt_ratio}; }
 

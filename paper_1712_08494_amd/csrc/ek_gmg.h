@@ -76,7 +76,7 @@ constexpr int kClkIter = 0, kClkCycles = 1, kClkSmooth = 2, kClkPasses = 3, kClk
 
 struct SmallArgs {
     GShape sh;
-    double tol, margin;  // margin: see kAxisMargin
+    double tol, margin;  // margin: what is aimed at, of the tolerance
     int maxit, fixed;    // fixed > 0: that many cycles, no test
     int step, history;   // step: the start is extrapolated in time from phi, prev, prev2
     double *prev, *prev2, *ctl;

@@ -22,10 +22,10 @@ def gpu():
 
 # A cycle (three sweeps on every grid and an exact coarsest solve) takes more than two thirds of a
 # residual: the cycle past the tolerance leaves less than a third of it.
-@pytest.mark.parametrize("shape,precision", [((50, 37, 29), "fp64"), ((4, 128, 128), "fp64"), ((26, 30, 22), "fp32")])
-def test_launched_cycles_end_well_below_the_tolerance(shape, precision):
-    print(f"per-axis multigrid, margin of the tolerance, {shape} {precision}", flush=True)
-    cfg, inp = wl.mixture_noise(shape=shape, precision=precision)
+@pytest.mark.parametrize("shape", [(50, 37, 29), (4, 128, 128), (26, 30, 22)])
+def test_launched_cycles_end_well_below_the_tolerance(shape):
+    print(f"per-axis multigrid, margin of the tolerance, {shape}", flush=True)
+    cfg, inp = wl.mixture_noise(shape=shape, precision="fp64")
     cfg.eps_b = 3.0 * cfg.eps_a
     sim = ek.EKSim(cfg, inp)
     for _ in range(4):
