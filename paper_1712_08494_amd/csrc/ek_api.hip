@@ -1715,8 +1715,9 @@ static ek_status configure(ek_ctx* c, const ek_params* p, const ek_particle* par
     c->esz = p->precision == EK_FP32 ? 4 : 8;
     // A lattice of at most 4096 sites that fits one workgroup's LDS with its coarse grids is
     // solved there by one launch: below that size every launch of a cycle is latency.  At the
-    // upper end 16^3 takes 152 us per step there against 268 with launches; a 4x4x128 column,
-    // whose coarsest launched grid (2x2x64) ten sweeps do not solve, 106 against 2840.
+    // upper end 16^3 takes 161 us per step there against 269 with launches in FP64 (122 and 186 in
+    // FP32), 32x32x4 162 and 261, 64x8x8 152 and 384, 16^3 between walls 240 and 329; a 4x4x128 column,
+    // whose coarsest launched grid (2x2x64) ten sweeps do not solve, 108 against 2840.
     if (p->poisson_solver != EK_POISSON_SOR && !c->fft && !c->batched) {
         const int dims[3] = {S.nx, S.ny, S.z1 - S.z0 + 1};
         const bool per[3] = {true, true, !S.walls};

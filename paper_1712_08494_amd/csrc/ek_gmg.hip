@@ -515,9 +515,9 @@ __device__ __forceinline__ double wg_sum(double v, double* sm, int tid, int nt) 
 // whole call and keeps their rows (neighbours, face permittivities, source) in registers;
 // LDS holds the potential, which neighbours read, and the coarse grids.  Bound by the
 // latency of its passes (LDS reads, the FP64 chain, a barrier: about 0.4 us), where a
-// launched pass costs 3 us.  A step of the 4 x 4 x 128 column takes 113 us (100 us of them
-// here: 25 us for the coarse grids and the inverse, 5 cycles of 12 us), against 2850 us
-// with launched cycles; of 16^3 in FP64 152 against 268 us.
+// launched pass costs 3 us.  A step of the 4 x 4 x 128 column in FP32 takes 108 us, 91 of
+// them here (28 for the rows, the coarse grids and the inverse, 4.9 cycles of 12.7),
+// against 2850 us with launched cycles; of 16^3 in FP64 161 against 269 us.
 // ------------------------------------------------------------------------------------
 // CLK: with its clock (a kernel of its own: the ticks cost the other one registers).
 template <typename T, int NS, int NT, bool CLK>

@@ -708,9 +708,9 @@ __device__ __forceinline__ void residual_body(const Scalars& S, const Fields<T>&
     v[2] = in ? p : 0.0;
 }
 
-// Lattices with an odd axis.  Each thread takes kResSites sites, kBlock apart (a workgroup covers
-// kResSites x kBlock consecutive sites), and sums them in order before the block reduction: fewer
-// records for the reducer to read.
+// Lattices without column kernels (an odd axis, a plane under 128 sites).  Each thread takes
+// kResSites sites, kBlock apart (a workgroup covers kResSites x kBlock consecutive sites), and sums
+// them in order before the block reduction: fewer records for the reducer to read.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_residual(Scalars S, Fields<T> F) {
     const unsigned nb = gridDim.x, b = blockIdx.x;
