@@ -381,8 +381,8 @@ __global__ __launch_bounds__(kBlock) void k_rp_finish(Scalars S, Reproj<T> P) {
     }
 }
 
-// Workgroups per box: one thread per box site while the chip is not full (2048 workgroups), at
-// least eight.
+// Workgroups per box: one thread per box site while the chip is not full (2048 workgroups in all);
+// with more particles than that leaves room for, eight, or one thread per site where that takes fewer.
 unsigned box_groups(const Scalars& S, int np) {
     const int B3 = S.rp_box * S.rp_box * S.rp_box, most = (B3 + kBlock - 1) / kBlock;
     return (unsigned)std::min(most, std::max(8, (2048 + np - 1) / np));
