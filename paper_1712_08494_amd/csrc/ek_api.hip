@@ -2535,8 +2535,9 @@ extern "C" ek_status ek_autotune_multigrid(ek_ctx* c, int32_t trial_steps, int32
 // own pinned memory, so faults, copies and the link overlap; pieces end on the destination's
 // 2 MiB boundaries, so that no two threads fault the same huge page.  A fresh 128 MiB
 // destination (a field of 256^3): 13.0 ms in one thread, 3.7 with six (4.4 with four, 4.0 with
-// eight, 4.8 with pieces of 1 MiB); 16 MiB: 1.17 and 0.82; 6 MiB: 0.5 both ways, and the pinned
-// pieces cost 1 ms on first use.
+// eight, 4.8 with pieces of 1 MiB); 16 MiB: 1.30 and 0.91; 8 MiB: 0.67 and 0.53; 6 MiB: 0.5 both
+// ways.  A context's first such read takes 1.3 to 1.6 ms more, for the pinned pieces: ten reads of 8 MiB
+// or four of 16 pay for them, one of 64 MiB does.
 // Memory that is already pinned, or on a device, takes the plain copy.
 //
 // The threads use a stream of their own that waits for the context's: a context may run on
